@@ -151,16 +151,17 @@ inline unsigned long long blk_sum(const unsigned long long* blk, int field, int 
 // steps enqueued.  Asynchronously (no host round trip) exactly max_iters
 // steps are enqueued, launches after convergence finding empty lists, and a
 // last kernel records in ctl->open_lists whether work was left over (read
-// back later by eik_async_status).
+// back later by eik_async_status) -- unless `report` is false: a later loop
+// of the call takes up what this one left over.
 // With `pageable` the lengths are copied into a stack buffer after each
 // chunk and the host waits for them before enqueuing the next chunk (no
 // pinned memory, no events; the device idles while the host enqueues).
 template <typename StepFn, typename CountsFn>
 inline eik_status run_loop(StepFn step, CountsFn counts, int nseg, int64_t max_iters, bool async,
-                           hipStream_t s, int64_t* steps, Ctl* ctl, bool pageable = false) {
+                           hipStream_t s, int64_t* steps, Ctl* ctl, bool pageable = false, bool report = true) {
     if (async) {
         for (int64_t t = 0; t < max_iters; ++t) HIP_TRY(step(t));
-        HIP_TRY(launch_loop_status(ctl, counts(max_iters), nseg, s));
+        if (report) HIP_TRY(launch_loop_status(ctl, counts(max_iters), nseg, s));
         *steps = max_iters;
         return EIK_OK;
     }
@@ -215,6 +216,25 @@ inline eik_status run_loop(StepFn step, CountsFn counts, int nseg, int64_t max_i
         slot ^= 1;
     }
     *steps = t;
+    return EIK_OK;
+}
+
+// Whether the list with the given `nseg` segment lengths holds anything, once
+// the stream has run what was enqueued (a synchronous call).
+inline eik_status list_total(const int* counts, int nseg, hipStream_t s, bool pageable, bool& open) {
+    int stack[HostSlots::kWords / 2];
+    int* words = stack;
+    if (nseg > HostSlots::kWords / 2) return fail(EIK_ERR_UNSUPPORTED, "too many list segments");
+    if (!pageable) {
+        HostSlots& hs = host_slots();
+        if (!hs.ok) return fail(EIK_ERR_DEVICE, "pinned host buffer allocation failed");
+        words = hs.words;
+    }
+    HIP_TRY(hipMemcpyAsync(words, counts, nseg * sizeof(int), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    long long sum = 0;
+    for (int k = 0; k < nseg; ++k) sum += words[k];
+    open = sum != 0;
     return EIK_OK;
 }
 

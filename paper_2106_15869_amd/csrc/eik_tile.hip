@@ -53,13 +53,8 @@ struct TileIter : Sched {
     const T* F;
     T* phi;
     uint8_t* lab;
-    const T* cells;  // tile-major cell values (k_build_cells), read by detection and the remedy
-    // early remedy visits during the update step (3D): per tile whether its
-    // last update visit left no active node, and the update visits finished
-    // in this launch and in the next one (cleared by this one)
-    uint8_t* done;
-    int* fin;
-    int* fin_clear;
+    const T* cells;  // tile-major cell values (k_build_cells), read by detection and the remedy visits
+    int early;       // merged update step: revisits count as early remedy evaluations
 };
 
 
@@ -195,8 +190,7 @@ __device__ __forceinline__ T eval_lds(const T* sphi, int L, T v, const Inst<T>& 
 
 
 // ---------------------------------------------------------------------------
-// A remedy visit (shared by the remedy launches and, in 3D, the early remedy
-// visits of the update step)
+// A remedy visit
 // ---------------------------------------------------------------------------
 // LDS of a remedy visit.
 template <typename T, int NT>
@@ -208,26 +202,24 @@ struct RemedyLds {
     int* face;         // faces a drop crossed
     int* evals;        // local-solver evaluations
     uint32_t* kmin;    // ordered: key of the smallest value that crossed a face (the caller sets kNoKey)
-    int* stop;         // POLL: lane 0's stop answer
-    int* written;      // values written back, or null (not counted)
+    int* unreached;    // whether a free node was +inf at the start (the tile's first visit)
+    int* written;      // values written back
 };
 
 // The remedy rule on tile t at (x0, y0, z0): stage its values with the halo
 // and its cell values, list the free nodes to recheck (all of them for
 // kAllFaces in the dirty faces, else those on the dirty faces), and iterate
-// until the list is empty, `inner` iterations ran or (POLL) poll() reached
-// stop_at (pending: nodes were still listed).  Lane 0 issues poll() every
-// other iteration and reads its value one iteration later, so the load's
-// latency hides behind an iteration instead of holding the workgroup.
+// until the list is empty or `inner` iterations ran (pending: nodes were
+// still listed).
 // The dirty faces are *s.mask, or lane 0's mask_in when set_mask.  Leaves the
 // new values in sphi with tl->dirty set for the changed nodes, and the
 // crossed faces, evaluations and (ordered) the crossing key in LDS.  Returns
 // the iterations run.
-template <typename T, int ND, int TX, int TY, int TZ, bool AN, bool POLL, typename Poll>
+template <typename T, int ND, int TX, int TY, int TZ, bool AN>
 __device__ __forceinline__ int remedy_visit(const T* cells, const T* phi, const Inst<T>& g, int t, int x0, int y0,
                                             int z0, int open, T eps, int inner, bool ordered, uint32_t mask_in,
                                             bool set_mask, const RemedyLds<T, Shape<ND, TX, TY, TZ>::NT>& s,
-                                            bool& pending, Poll poll, int stop_at) {
+                                            bool& pending) {
     using S = Shape<ND, TX, TY, TZ>;
     const T inf = pos_inf<T>();
     TileLists<S::NT>& tl = *s.tl;
@@ -252,8 +244,8 @@ __device__ __forceinline__ int remedy_visit(const T* cells, const T* phi, const 
     if (threadIdx.x == 0) {
         *s.face = 0;
         *s.evals = 0;
-        if (s.written) *s.written = 0;
-        if (POLL) *s.stop = 0;
+        *s.written = 0;
+        *s.unreached = 0;
         if (set_mask) *s.mask = mask_in;
         tl.cnt[0] = tl.cnt[1] = tl.cnt[2] = 0;
     }
@@ -269,31 +261,26 @@ __device__ __forceinline__ int remedy_visit(const T* cells, const T* phi, const 
         int x, y, z, L;
         node_loc<ND, TX, TY, TZ>(nn, x, y, z, L);
         const int E = edge_bits<ND, TX, TY, TZ>(x, y, z) & open;
-        if (cell_free<T, AN>(s.sH[nn]) && ((m & kAllFaces) || (E & static_cast<int>(m))))
+        if (!cell_free<T, AN>(s.sH[nn])) continue;
+        if (!(sphi[L] < inf)) *s.unreached = 1;
+        if ((m & kAllFaces) || (E & static_cast<int>(m)))
             tl.list[0][atomicAdd(&tl.cnt[0], 1)] = static_cast<uint16_t>(nn);
     }
     __syncthreads();
     pending = false;
     int my_evals = 0, fm = 0;
     T kmin = inf;  // smallest value that crossed a face (order key of the pushes)
-    int polled = 0;  // lane 0 (POLL): the value of the last poll()
     int it = 0;
     for (;; ++it) {
         const int ncur = tl.cnt[it % 3];
         if (ncur == 0) break;
-        if (it == inner || (POLL && *s.stop)) {
+        if (it == inner) {
             pending = true;
             break;
         }
         const int cb = it & 1, nb = cb ^ 1;
         int* ncnt = &tl.cnt[(it + 1) % 3];
-        if (threadIdx.x == 0) {
-            tl.cnt[(it + 2) % 3] = 0;
-            if (POLL) {
-                if (it & 1) polled = poll();
-                else if (it > 0) *s.stop = polled >= stop_at ? 1 : 0;
-            }
-        }
+        if (threadIdx.x == 0) tl.cnt[(it + 2) % 3] = 0;
         for (int i = threadIdx.x; i < ncur; i += kBlock) {
             const int q = tl.list[cb][i];
             tl.flag[cb][q] = 0u;
@@ -379,25 +366,14 @@ __device__ __forceinline__ void remedy_write_back(T* phi, const Inst<T>& g, int 
         phi[g.node_base + ((z0 + z) * g.ny + (y0 + y)) * g.nx + (x0 + x)] = s.sphi[L];
         ++my_written;
     }
-    if (s.written && my_written) atomicAdd(s.written, my_written);
+    if (my_written) atomicAdd(s.written, my_written);
 }
 
 // ---------------------------------------------------------------------------
 // STEP 2 on tiles
 // ---------------------------------------------------------------------------
-// Resident workgroups per CU for the update step: six for 8^3 float tiles
-// (two nodes per lane), so that all 1536 default workgroups of a launch are
-// resident at once (eighty registers, one value spilled); with early remedy visits a
-// workgroup that waited for a slot would start its visit late and hold the
-// launch.  Others unconstrained.
-template <int ND, int NPT, typename T>
-constexpr int update_blocks_per_cu() {
-    return ND == 3 && NPT == 2 && sizeof(T) == 4 ? 6 : 1;
-}
-
 template <typename T, int ND, int TX, int TY, int TZ, bool AN>
-__global__ __launch_bounds__(kBlock, (update_blocks_per_cu<ND, Shape<ND, TX, TY, TZ>::NPT, T>())) void k_tile_update(
-    TileIter<T> a, BatchGeom<T> bg, T eps, int inner, TileIter<T> e, int early_inner) {
+__global__ __launch_bounds__(kBlock) void k_tile_update(TileIter<T> a, BatchGeom<T> bg, T eps, int inner) {
     using S = Shape<ND, TX, TY, TZ>;
     __shared__ T sphi[S::NL];
     __shared__ uint8_t sl[S::NL];
@@ -409,21 +385,8 @@ __global__ __launch_bounds__(kBlock, (update_blocks_per_cu<ND, Shape<ND, TX, TY,
     __shared__ int s_face;
     __shared__ int s_evals;
     __shared__ int s_written;
-    __shared__ int s_elen[kSub];
-    __shared__ uint32_t s_emask;
-    __shared__ int s_stop;
     const T inf = pos_inf<T>();
     const uint32_t ntag = launch_tag(a);
-    // early remedy visits exist in 3D float only (compiled out elsewhere)
-    const bool early = ND == 3 && sizeof(T) == 4 && e.done != nullptr;
-    if (early) {
-        if (blockIdx.x == 0 && threadIdx.x < kSub) {
-            e.zero_count[threadIdx.x * kPad] = 0;
-            e.zero_fetch[threadIdx.x * kPad] = 0;
-            if (threadIdx.x == 0) *e.fin_clear = 0;
-        }
-        if (threadIdx.x < kSub) s_elen[threadIdx.x] = e.cur.count[threadIdx.x * kPad];
-    }
     const int n = list_open(a, s_len);
     launch_stats(a, n);
     // workgroups of group k take entries of sub-list k one at a time
@@ -612,15 +575,7 @@ __global__ __launch_bounds__(kBlock, (update_blocks_per_cu<ND, Shape<ND, TX, TY,
             const int d = threadIdx.x;
             const int fmask = s_face;
             if (d == 6) {
-                if (any_active) {
-                    push_tile(a.next, a.tstamp, t, ntag);
-                } else if (early) {
-                    // the tile's update work is done for now: queue its first
-                    // remedy visit (every node) for the idle workgroups
-                    e.done[t] = 1;
-                    atomicOr(e.mask_next + t, kAllFaces);
-                    push_tile(e.next, e.tstamp, t, ntag);
-                }
+                if (any_active) push_tile(a.next, a.tstamp, t, ntag);
             } else if (d < 2 * ND && (fmask & (1 << d))) {
                 push_tile(a.next, a.tstamp, neighbour_tile(g, t, d), ntag);
             }
@@ -629,7 +584,6 @@ __global__ __launch_bounds__(kBlock, (update_blocks_per_cu<ND, Shape<ND, TX, TY,
             evals += static_cast<unsigned long long>(s_evals);
             inner_sum += static_cast<unsigned long long>(it);
             written += static_cast<unsigned long long>(s_written);
-            if (early) atomicAdd(e.fin, 1);
         }
         __syncthreads();
     }
@@ -639,64 +593,6 @@ __global__ __launch_bounds__(kBlock, (update_blocks_per_cu<ND, Shape<ND, TX, TY,
         stat_add(a.blkstat, SF_INNER2, inner_sum);
         stat_add(a.blkstat, SF_WRITTEN2, written);
     }
-    // Early remedy: workgroups that had no update visit in this launch run
-    // remedy visits (first-in first-out, at most early_inner inner
-    // iterations) on tiles whose update work is done, behind the front; the
-    // remedy after the update step (detection over every node, then the
-    // ordered loop) still decides the fixed point.
-    if (!early || visits) return;
-    const int elen = s_elen[k];
-    unsigned long long eevals = 0;
-    for (;;) {
-        if (threadIdx.x == 0) {
-            // no new early visit once the launch's update visits are all done
-            const bool over = __hip_atomic_load(e.fin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= n;
-            const int ei = over ? elen : atomicAdd(e.cur.fetch + k * kPad, 1);  // workgroups arrive at any time
-            const int tt = ei < elen ? e.cur.data[static_cast<size_t>(k) * e.cur.cap + ei] : -1;
-            if (tt >= 0) {
-                s_emask = e.mask_cur[tt];  // set by an earlier launch; no writer during this one
-                e.mask_cur[tt] = 0u;
-            }
-            s_slot = tt;
-        }
-        __syncthreads();
-        const int t = s_slot;
-        __syncthreads();
-        if (t < 0) break;
-        const Inst<T> g = inst_of(bg, t);
-        const int lt = t - g.tile_base;
-        const int tx = lt % g.ntx, ty = (lt / g.ntx) % g.nty, tz = lt / (g.ntx * g.nty);
-        const int x0 = tx * TX, y0 = ty * TY, z0 = tz * (ND == 3 ? TZ : 1);
-        const int open = open_bits<ND, TX, TY, TZ>(g, x0, y0, z0);
-        const RemedyLds<T, S::NT> rl{sphi, sH, &tl, &s_emask, &s_face, &s_evals, nullptr, &s_stop, nullptr};
-        bool pending;
-        // stop once the launch's update visits are all done
-        remedy_visit<T, ND, TX, TY, TZ, AN, true>(
-            e.cells, a.phi, g, t, x0, y0, z0, open, eps, early_inner, false, 0u, false, rl, pending,
-            [&] { return __hip_atomic_load(e.fin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }, n);
-        // a face whose neighbour tile is done with its update work marks that
-        // tile; the others get their first visit when they are done
-        if (threadIdx.x < 7) {
-            const int d = threadIdx.x;
-            if (d == 6) {
-                if (pending) {
-                    atomicOr(e.mask_next + t, kAllFaces);
-                    push_tile(e.next, e.tstamp, t, ntag);
-                }
-            } else if (d < 2 * ND && (s_face & (1 << d))) {
-                const int tn = neighbour_tile(g, t, d);
-                if (e.done[tn]) {
-                    atomicOr(e.mask_next + tn, 1u << (d ^ 1));
-                    push_tile(e.next, e.tstamp, tn, ntag);
-                }
-            }
-        }
-        remedy_write_back<T, ND, TX, TY, TZ>(a.phi, g, x0, y0, z0, rl);
-        if (threadIdx.x == 0) eevals += static_cast<unsigned long long>(s_evals);
-        __syncthreads();
-        break;  // one early visit per workgroup and launch: the launch ends with its update visits
-    }
-    if (threadIdx.x == 0) stat_add(a.blkstat, SF_CHECK, eevals);
 }
 
 // ---------------------------------------------------------------------------
@@ -753,6 +649,18 @@ __global__ __launch_bounds__(kBlock) void k_tile_detect(TileIter<T> a, BatchGeom
 // the next iteration when the new value lies below theirs (otherwise their
 // update cannot change: the node is not upwind of them), and a face neighbour
 // below the halo value marks that face dirty in the tile across it.
+// Statistics of a workgroup's visits, by the loop it ran in.
+__device__ __forceinline__ void visit_stats(const Sched& a, unsigned long long evals, unsigned long long early,
+                                            unsigned long long visits, unsigned long long inner,
+                                            unsigned long long written) {
+    const bool upd = a.phase == 0;
+    stat_add(a.blkstat, upd ? SF_EVALS2 : SF_EVALS3, evals);
+    stat_add(a.blkstat, SF_CHECK, early);
+    stat_add(a.blkstat, upd ? SF_VISITS2 : SF_VISITS3, visits);
+    stat_add(a.blkstat, upd ? SF_INNER2 : SF_INNER3, inner);
+    stat_add(a.blkstat, upd ? SF_WRITTEN2 : SF_WRITTEN3, written);
+}
+
 // Resident workgroups per CU for float tiles (the inner iterations are
 // latency-bound; occupancy against spilled registers, measured): eight for
 // tiles of one node per lane, six for two (the 8^3 tile: eight spill at
@@ -776,6 +684,7 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
     __shared__ int s_written;
     __shared__ uint32_t s_mask;
     __shared__ uint32_t s_key, s_kmin;
+    __shared__ int s_unreached;
     const uint32_t ntag = launch_tag(a);
     // ordered mode: k_tile_split has moved this launch's tiles into the work
     // list (the rest went on to the next list)
@@ -787,7 +696,7 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
     const TList src = from_work ? a.work : a.cur;
     const int k = blockIdx.x & (kSub - 1);
     const int len = from_work ? s_wlen[k] : s_len[k];
-    unsigned long long evals = 0, inner_sum = 0, written = 0, visits = 0;
+    unsigned long long evals = 0, early = 0, inner_sum = 0, written = 0, visits = 0;
     for (bool first = true;; first = false) {
         if (threadIdx.x == 0) {
             const int e = fetch_index(src, k, len, first);
@@ -823,11 +732,10 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
             }
             s_kmin = kNoKey;
         }
-        const RemedyLds<T, S::NT> rl{sphi, sH, &tl, &s_mask, &s_face, &s_evals, &s_kmin, nullptr, &s_written};
+        const RemedyLds<T, S::NT> rl{sphi, sH, &tl, &s_mask, &s_face, &s_evals, &s_kmin, &s_unreached, &s_written};
         bool pending;
-        const int it = remedy_visit<T, ND, TX, TY, TZ, AN, false>(a.cells, a.phi, g, t, x0, y0, z0, open, eps, inner,
-                                                                  a.ordered, mask_in, !from_work, rl, pending,
-                                                                  [] { return 0; }, 0);
+        const int it = remedy_visit<T, ND, TX, TY, TZ, AN>(a.cells, a.phi, g, t, x0, y0, z0, open, eps, inner,
+                                                           a.ordered, mask_in, !from_work, rl, pending);
         // scheduling, one lane per target tile (see the update kernel); the
         // targets are read by the next launch, so these atomics may overlap
         // the write-back below
@@ -849,17 +757,13 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
         remedy_write_back<T, ND, TX, TY, TZ>(a.phi, g, x0, y0, z0, rl);
         __syncthreads();
         if (threadIdx.x == 0) {
-            evals += static_cast<unsigned long long>(s_evals);
+            // a revisit of the merged update step corrects values: early remedy
+            (a.early && !s_unreached ? early : evals) += static_cast<unsigned long long>(s_evals);
             inner_sum += static_cast<unsigned long long>(it);
             written += static_cast<unsigned long long>(s_written);
         }
     }
-    if (threadIdx.x == 0 && visits) {
-        stat_add(a.blkstat, SF_EVALS3, evals);
-        stat_add(a.blkstat, SF_VISITS3, visits);
-        stat_add(a.blkstat, SF_INNER3, inner_sum);
-        stat_add(a.blkstat, SF_WRITTEN3, written);
-    }
+    if (threadIdx.x == 0 && visits) visit_stats(a, evals, early, visits, inner_sum, written);
 }
 
 
@@ -897,11 +801,11 @@ __global__ __launch_bounds__(kBlock) void k_build_cells(BatchGeom<T> bg, const T
 // STEP 1 helpers
 // ---------------------------------------------------------------------------
 
-// Initial tile list: tiles holding a grid neighbour of a source (claimed with
-// tag 1).
+// Initial tile list: tiles holding a grid neighbour of a source (a's next
+// list and tag), every node of them to be evaluated, ordered by the source's
+// value.
 template <typename T>
-__global__ void k_seed_tiles(BatchGeom<T> bg, int nd, int tx_, int ty_, int tz_, SrcBatch<T> b,
-                             uint32_t* tstamp, TList out) {
+__global__ void k_seed_tiles(Sched a, BatchGeom<T> bg, int nd, int tx_, int ty_, int tz_, SrcBatch<T> b) {
     const int k = threadIdx.x;
     if (k >= b.count) return;
     const Inst<T> g = bg.ninst == 1 ? bg.one : bg.table[b.inst[k]];
@@ -911,12 +815,14 @@ __global__ void k_seed_tiles(BatchGeom<T> bg, int nd, int tx_, int ty_, int tz_,
     for (int d = 0; d < 2 * nd; ++d) {
         const int X = x + dx[d], Y = y + dy[d], Z = z + dz[d];
         if (X < 0 || X >= g.nx || Y < 0 || Y >= g.ny || Z < 0 || Z >= g.nz) continue;
-        push_tile(out, tstamp, g.tile_base + ((Z / tz_) * g.nty + (Y / ty_)) * g.ntx + (X / tx_), 1u);
+        const int t = g.tile_base + ((Z / tz_) * g.nty + (Y / ty_)) * g.ntx + (X / tx_);
+        atomicOr(a.mask_next + t, kAllFaces);
+        push_keyed(a, t, 1u, order_key(b.val[k]));
     }
 }
 
-// Initial tile list holding every tile (used when there are many sources):
-// tile t is entry t / kSub of sub-list t % kSub.
+// Initial tile list holding every tile (the update step alone, many
+// sources): tile t is entry t / kSub of sub-list t % kSub.
 __global__ void k_seed_all_tiles(int ntiles, uint32_t* tstamp, TList out) {
     for (int t = blockIdx.x * kBlock + threadIdx.x; t < ntiles; t += gridDim.x * kBlock) {
         tstamp[t] = 1u;
@@ -935,8 +841,6 @@ struct TileWs {
     uint8_t* lab;
     void* cells;        // tile-major cell values (ntiles x tile nodes)
     SchedWs q;          // lists, stamps, masks, keys, histograms, work lists
-    SchedWs eq;         // 3D: the early remedy's lists, stamps and dirty-face masks
-    uint8_t* done;      // 3D: per tile, update work done
     void* table;        // instance table (batches of more than one instance)
     int* tile_inst;     // instance of every tile (idem)
     void* table_u;      // the same for the update step's tiling (2D, see solve_tile)
@@ -958,10 +862,6 @@ TileWs tile_layout(char* base, int64_t n, int64_t ntiles, size_t ninst, size_t i
     w.lab = reinterpret_cast<uint8_t*>(take(static_cast<size_t>(n)));
     w.cells = take(cell_bytes);
     w.q = sched_layout(take, ntiles);
-    if (!two_tilings) {  // 3D (one tiling for both steps): early remedy
-        w.eq = early_layout(take, ntiles);
-        w.done = reinterpret_cast<uint8_t*>(take(static_cast<size_t>(ntiles)));
-    }
     if (ninst > 1) {
         w.table = take(inst_bytes * ninst);
         w.tile_inst = reinterpret_cast<int*>(take(4 * static_cast<size_t>(ntiles)));
@@ -988,10 +888,8 @@ bool update_tiling(const Batch& b, const eik_options& o, TileCfg& cu) {
 // Launches of `gt` persistent workgroups (a multiple of kSub, at most GT).
 template <typename T, int ND, int TX, int TY, int TZ, bool AN>
 struct TileKernels {
-    static hipError_t update(const TileIter<T>& a, const BatchGeom<T>& g, T eps, int inner, int gt,
-                             const TileIter<T>& e, int early_inner, hipStream_t s) {
-        hipLaunchKernelGGL((k_tile_update<T, ND, TX, TY, TZ, AN>), dim3(gt), dim3(kBlock), 0, s, a, g, eps, inner, e,
-                           early_inner);
+    static hipError_t update(const TileIter<T>& a, const BatchGeom<T>& g, T eps, int inner, int gt, hipStream_t s) {
+        hipLaunchKernelGGL((k_tile_update<T, ND, TX, TY, TZ, AN>), dim3(gt), dim3(kBlock), 0, s, a, g, eps, inner);
         return hipGetLastError();
     }
     static hipError_t detect(const TileIter<T>& a, const BatchGeom<T>& g, T eps, int gt, hipStream_t s) {
@@ -1013,8 +911,7 @@ struct TileKernels {
 
 template <typename T>
 struct TileOps {
-    hipError_t (*update)(const TileIter<T>&, const BatchGeom<T>&, T, int, int, const TileIter<T>&, int,
-                         hipStream_t) = nullptr;
+    hipError_t (*update)(const TileIter<T>&, const BatchGeom<T>&, T, int, int, hipStream_t) = nullptr;
     hipError_t (*detect)(const TileIter<T>&, const BatchGeom<T>&, T, int, hipStream_t) = nullptr;
     hipError_t (*remedy)(const TileIter<T>&, const BatchGeom<T>&, T, int, int, hipStream_t) = nullptr;
     hipError_t (*cells)(const BatchGeom<T>&, const T*, const uint8_t*, T*, hipStream_t) = nullptr;
@@ -1111,28 +1008,29 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
                       hipStream_t s, eik_stats* st) {
     const bool async = (o.flags & EIK_FLAG_ASYNC) != 0;
     const bool pageable = (o.flags & kFlagPageable) != 0;
+    const bool skip_remedy = (o.flags & EIK_FLAG_SKIP_REMEDY) != 0;
+    // The update step alone (a diagnostic, and 3D solves that ask for it);
+    // else the update step corrects values as it goes (see below).
+    const bool alone = skip_remedy || (b.nd == 3 && (o.flags & EIK_FLAG_NO_EARLY_REMEDY));
     const TileCfg c = b.cfg;
     TileOps<T> k;
     if (!select_ops<T>(b.nd, c, b.inst[0].aniso != 0, k))
         return fail(EIK_ERR_INVALID_ARGUMENT, b.inst[0].aniso ? "per-axis spacing needs the default tile shape"
                                                               : "unsupported tile shape");
     TileWs w = tile_layout(ws, b.n, b.ntiles, b.inst.size(), sizeof(Inst<T>), b.nd == 2, cell_array_bytes(b, sizeof(T)));
-    // the update step's tiling (the same unless update_tiling says otherwise)
+    // the tiling of the update step alone (the same unless update_tiling says otherwise)
     TileCfg cu = c;
-    const bool two = update_tiling(b, o, cu);
+    const bool two = alone && update_tiling(b, o, cu);
     const Batch bu = two ? with_tiles(b, cu) : Batch{};
     const Batch& B2 = two ? bu : b;
     TileOps<T> ku = k;
     if (two && !select_ops<T>(b.nd, cu, false, ku)) return fail(EIK_ERR_INVALID_ARGUMENT, "unsupported tile shape");
     const int64_t cap = o.max_iters > 0 ? o.max_iters : 4 * b.n + 64;
-    // Inner iterations per tile visit.  In 2D an update visit stops after the
-    // iterations a front needs to cross the tile along an axis (one per node
-    // with the 2D two-phase iteration): the front still advances a tile per
-    // launch, and no visit holds its launch for a diagonal crossing (2D
-    // lognormal 4096^2, 16 x 16 tiles: update 34 -> 19 ms).  In 3D the cut
-    // visits leave more to the remedy than they save (256^3 maze), so update
-    // and remedy visits run until their lists empty (4 x the sum of the sides
-    // is a safety cap).
+    // Inner iterations per tile visit: visits run until their lists empty
+    // (4 x the sum of the sides is a safety cap), except in the 2D update step
+    // alone, whose visits stop after the iterations a front needs to cross the
+    // tile along an axis (the front still advances a tile per launch, and no
+    // visit holds its launch for a diagonal crossing).
     const int inner = o.inner_iters > 0 ? o.inner_iters : 4 * (c.tx + c.ty + c.tz);
     const int side_u = std::max(cu.tx, std::max(cu.ty, cu.tz));
     const int inner_upd = o.inner_iters > 0 ? o.inner_iters : (b.nd == 2 ? side_u : inner);
@@ -1158,8 +1056,6 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
     HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return sched_clear(w.q, s); }));
     launched += 7;
     const bool ordered = (o.flags & EIK_FLAG_FIFO_REMEDY) == 0;
-    const bool early = b.nd == 3 && sizeof(T) == 4 && !two &&
-                       !(o.flags & (EIK_FLAG_NO_EARLY_REMEDY | EIK_FLAG_SKIP_REMEDY));
     std::vector<SrcBatch<T>> batches;
     for (size_t q = 0; q < b.src.size(); q += kMaxSrcBatch) {
         SrcBatch<T> sb{};
@@ -1174,110 +1070,121 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
     for (auto& sb : batches)
         HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return launch_seed<T>(phi, w.lab, sb, s); }));
     launched += static_cast<int64_t>(batches.size());
-    auto list_of = [&](int64_t t) { return w.q.list_of(t); };
-    if (batches.size() <= 8) {
-        // tiles next to the sources
-        for (auto& sb : batches)
-            HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] {
-                hipLaunchKernelGGL(k_seed_tiles<T>, dim3(1), dim3(kMaxSrcBatch), 0, s, geom_u, b.nd, cu.tx, cu.ty, cu.tz,
-                                   sb, w.q.tstamp, list_of(0));
-                return hipGetLastError();
-            }));
-        launched += static_cast<int64_t>(batches.size());
-    } else {
-        // many sources: start from every tile; tiles with nothing to do drop out
-        HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] {
-            hipLaunchKernelGGL(k_seed_all_tiles, dim3(std::min((ntiles_u + kBlock - 1) / kBlock, 1024)), dim3(kBlock),
-                               0, s, ntiles_u, w.q.tstamp, list_of(0));
-            return hipGetLastError();
-        }));
-        launched += 1;
-    }
 
     const T eT = static_cast<T>(eps);
-    int64_t gl = 0;  // launches in the tag chain so far (selects the tag slot)
-    // launch t drains list t and fills list t + 1; lists alternate two buffers
-    // and three counter sets (the set of list t + 2 is cleared by launch t)
+    // The launches of a solve form one chain: launch t drains list t and fills
+    // list t + 1; lists alternate two buffers and three counter sets (the set
+    // of list t + 2 is cleared by launch t).
     auto iter_args = [&](int64_t t, int phase) {
         TileIter<T> a{};
-        sched_fill(a, w.q, t, ordered && phase == 1, omin, static_cast<int>((gl + t) & 1), phase, w.ctl,
+        sched_fill(a, w.q, t, ordered && !(alone && phase == 0), omin, static_cast<int>(t & 1), phase, w.ctl,
                    w.blkstat);
         a.F = F;
         a.phi = phi;
         a.lab = w.lab;
         a.cells = static_cast<const T*>(w.cells);
+        a.early = !alone && phase == 0 && b.nd == 3 && sizeof(T) == 4 ? 1 : 0;
         return a;
     };
-    auto counts = [&](int64_t t) { return w.q.count_of(static_cast<int>(t % 3)); };
-    if (early) {
-        // cell values (sources are fixed by now) and the early remedy's lists
-        HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return k.cells(geom, F, w.lab, static_cast<T*>(w.cells), s); }));
-        HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return early_clear(w.eq, s); }));
-        HIP_TRY(timed(prof, EIK_KERNEL_OTHER,
-                      [&] { return launch_zero_words(w.done, align_up(static_cast<size_t>(b.ntiles), 4), s); }));
-        launched += 3;
-    }
-    auto early_args = [&](int64_t t) {
-        TileIter<T> e{};
-        if (!early) return e;
-        sched_fill(e, w.eq, t, false, omin, static_cast<int>((gl + t) & 1), 1, w.ctl, w.blkstat);
-        e.phi = phi;
-        e.cells = static_cast<const T*>(w.cells);
-        e.done = w.done;
-        e.fin = &w.ctl->cnt[t % 3];
-        e.fin_clear = &w.ctl->cnt[(t + 1) % 3];
-        return e;
+    // a kernel that only adds to list t, before launch t drains it (beside
+    // launch t - 1, whose tag it claims tiles with)
+    auto producer_args = [&](int64_t t, int phase) {
+        TileIter<T> a = iter_args(t + 1, phase);
+        a.next = w.q.list_of(t);
+        a.mask_next = w.q.tmask + static_cast<size_t>(t & 1) * w.q.ntiles;
+        a.key_next = w.q.keys + static_cast<size_t>(t & 1) * w.q.ntiles;
+        a.hist_next = w.q.hist_of(static_cast<int>(t % 3));
+        a.ordered = ordered ? 1 : 0;
+        a.first = 0;
+        return a;
     };
-    // inner iterations of an early remedy visit (maze 256^3 / layered 192^3:
-    // 16 gave 14.1 / 5.9 ms, 32 and 64 14.7 / 6.3 ms: deeper visits hold the
-    // update launch longer than they shorten the remedy loop)
-    const int early_inner = 16;
+    auto detect = [&](int64_t t) {
+        return timed(prof, EIK_KERNEL_DETECT, [&] { return k.detect(producer_args(t, 1), geom, eT, gt, s); });
+    };
+    const int split_blocks = split_blocks_of(b.ntiles);
+    auto visits = [&](int64_t t, int phase, bool first) {
+        TileIter<T> a = iter_args(t, phase);
+        a.first = first ? 1 : 0;
+        if (ordered) {
+            const hipError_t e = timed(prof, EIK_KERNEL_OTHER, [&] {
+                hipLaunchKernelGGL(k_tile_split, dim3(split_blocks), dim3(kBlock), 0, s, static_cast<const Sched&>(a));
+                return hipGetLastError();
+            });
+            if (e != hipSuccess) return e;
+        }
+        return timed(prof, phase == 0 ? EIK_KERNEL_UPDATE : EIK_KERNEL_REMEDY,
+                     [&] { return k.remedy(a, geom, eT, inner, gt, s); });
+    };
+    auto counts = [&](int64_t t) { return w.q.count_of(static_cast<int>(t % 3)); };
 
+    // Cell values for the visits and detection (sources are fixed by now).
+    if (!skip_remedy) {
+        HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return k.cells(geom, F, w.lab, static_cast<T*>(w.cells), s); }));
+        launched += 1;
+    }
+    // Initial list: the tiles next to the sources; with many sources a dense
+    // pass finds them.  (One launch per 64 sources up to 8 of them, about what
+    // the dense pass over a 4 M node grid costs.)
+    if (batches.size() <= 8) {
+        TileIter<T> a = producer_args(0, 0);
+        if (alone) a.ordered = 0;
+        for (auto& sb : batches)
+            HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] {
+                hipLaunchKernelGGL(k_seed_tiles<T>, dim3(1), dim3(kMaxSrcBatch), 0, s, static_cast<const Sched&>(a),
+                                   geom_u, b.nd, cu.tx, cu.ty, cu.tz, sb);
+                return hipGetLastError();
+            }));
+        launched += static_cast<int64_t>(batches.size());
+    } else if (alone) {
+        HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] {
+            hipLaunchKernelGGL(k_seed_all_tiles, dim3(std::min((ntiles_u + kBlock - 1) / kBlock, 1024)), dim3(kBlock),
+                               0, s, ntiles_u, w.q.tstamp, w.q.list_of(0));
+            return hipGetLastError();
+        }));
+        launched += 1;
+    } else {
+        HIP_TRY(detect(0));
+        launched += 1;
+    }
+
+    // STEP 2.  By default the update step corrects as it goes: from the
+    // sources outward, tile visits by the remedy rule (a node that drops lists
+    // its neighbours again), lowest keys first, until no tile is queued.  A
+    // front that first converged whole tiles without looking back (the update
+    // step alone) left 43 evaluations per node to the remedy on a 2D
+    // lognormal 4096^2 grid; corrected while the front is near, the same
+    // solution takes 36 in all (45.5 -> 28.3 ms; 256^3 maze 13.2 -> 9.1 ms,
+    // layered 192^3 5.4 -> 3.3 ms).
     int64_t n2 = 0;
     eik_status rc = run_loop(
         [&](int64_t t) {
-            return timed(prof, EIK_KERNEL_UPDATE, [&] {
-                return ku.update(iter_args(t, 0), geom_u, eT, inner_upd, gt, early_args(t), early_inner, s);
-            });
+            if (!alone) return visits(t, 0, false);
+            return timed(prof, EIK_KERNEL_UPDATE,
+                         [&] { return ku.update(iter_args(t, 0), geom_u, eT, inner_upd, gt, s); });
         },
-        counts, kSub * kPad, cap, async, s, &n2, w.ctl, pageable);
-    gl += n2;
-    launched += n2;
-    if (rc == EIK_OK && !(o.flags & EIK_FLAG_SKIP_REMEDY)) {
-        // tile-major cell values for detection and the remedy; detection
-        // fills list 0 of the remedy loop
-        if (!early) {
-            HIP_TRY(timed(prof, EIK_KERNEL_OTHER,
-                          [&] { return k.cells(geom, F, w.lab, static_cast<T*>(w.cells), s); }));
-            launched += 1;
-        }
-        HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return launch_zero_words(w.q.counters, kCounterBytes, s); }));
-        TileIter<T> d = iter_args(0, 1);  // only `next` (list 0), its masks and the tag are used
-        d.next = list_of(0);
-        d.mask_next = w.q.tmask;  // read by remedy launch 0
-        d.key_next = w.q.keys;
-        d.hist_next = w.q.hist_of(0);
-        d.first = 0;
-        d.tag_slot = static_cast<int>(gl & 1);
-        HIP_TRY(timed(prof, EIK_KERNEL_DETECT, [&] { return k.detect(d, geom, eT, gt, s); }));
-        gl += 1;
-        launched += 2;
+        counts, kSub * kPad, cap, async, s, &n2, w.ctl, pageable, alone);
+    launched += (ordered && !alone ? 2 : 1) * n2;
+    if (rc == EIK_OK && !skip_remedy) {
+        // STEP 3: detection adds to the list the next launch drains (what an
+        // asynchronous update step left over is still in it), then the remedy
+        // loop.  A synchronous call reads the list's length first: after the
+        // correcting update step it is empty.
+        HIP_TRY(detect(n2));
+        launched += 1;
         int64_t n3 = 0;
-        const int split_blocks = split_blocks_of(b.ntiles);
-        rc = run_loop(
-            [&](int64_t t) {
-                const TileIter<T> a = iter_args(t, 1);
-                if (ordered) {
-                    const hipError_t e = timed(prof, EIK_KERNEL_OTHER, [&] {
-                        hipLaunchKernelGGL(k_tile_split, dim3(split_blocks), dim3(kBlock), 0, s, static_cast<const Sched&>(a));
-                        return hipGetLastError();
-                    });
-                    if (e != hipSuccess) return e;
-                }
-                return timed(prof, EIK_KERNEL_REMEDY, [&] { return k.remedy(a, geom, eT, inner, gt, s); });
-            },
-            counts, kSub * kPad, cap, async, s, &n3, w.ctl, pageable);
-        launched += (ordered ? 2 : 1) * n3;
+        bool open = true;
+        if (!async && !alone) {
+            rc = list_total(counts(n2), kSub * kPad, s, pageable, open);
+            if (rc != EIK_OK) return rc;
+        }
+        if (open) {
+            rc = run_loop(
+                [&](int64_t t) {
+                    return visits(n2 + t, 1, t == 0);
+                },
+                [&](int64_t t) { return counts(n2 + t); }, kSub * kPad, cap, async, s, &n3, w.ctl, pageable);
+            launched += (ordered ? 2 : 1) * n3;
+        }
     }
     if (async) return rc;
     Results res;

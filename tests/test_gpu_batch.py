@@ -220,3 +220,26 @@ def test_schedule_options_keep_the_fixed_point(P, order_min, workgroups):
         part = pb[k * P.F.size:(k + 1) * P.F.size].reshape(P.F.shape)
         assert np.array_equal(fin, np.isfinite(part))
         assert np.max(np.abs(part[fin] - ref[fin])) <= 1e-5 * ref[fin].max()
+
+
+@pytest.mark.parametrize("fifo", [False, True])
+@pytest.mark.parametrize("P", [W.lognormal_2d(300, seed=4), W.maze_3d(40, seed=3), W.paper_example(1, 300)],
+                         ids=lambda P: P.name)
+def test_async_remedy_takes_up_what_the_update_budget_left(P, fifo):
+    """An asynchronous solve whose budget ends the update step early: the
+    remedy loop drains what is still listed (its own budget is as long), so
+    the call converges and reports so.  Example 1 at 300^2 has more than 512
+    sources, whose tiles the dense seeding pass finds."""
+    F = torch.from_numpy(P.F).to(DEV)
+    _, st = eik.solve(F, P.h, P.sources, source_values=P.source_values, fifo=fifo, stats=True)
+    budget = (2 * st["step2_iters"]) // 3
+    print(f"[case] {P.name} fifo {fifo}: update step {st['step2_iters']} launches, budget {budget}", flush=True)
+    assert st["step3_iters"] == 0 and budget < st["step2_iters"]
+    out = torch.empty_like(F)
+    ws = torch.empty(eik.eik_workspace_size(P.F.shape, eik.make_options(eik.EIK_FLOAT32, "tile", fifo=fifo)),
+                     dtype=torch.uint8, device=DEV)
+    eik.solve(F, P.h, P.sources, source_values=P.source_values, fifo=fifo, out=out, workspace=ws, max_iters=budget,
+              async_=True)
+    eik.check_async(ws)
+    ref = oracle.fmm(P.F.astype(np.float64), P.h, P.sources, values=P.source_values)
+    assert np.max(np.abs(out.cpu().numpy() - ref)) <= 1e-5 * ref.max()
