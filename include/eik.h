@@ -84,21 +84,22 @@ enum {
     /* Bracket every kernel launch with HIP events on the solve's stream and
        report per-kind device time in eik_stats (adds host overhead). */
     EIK_FLAG_PROFILE = 8u,
-    /* Tile variant: run the remedy loop first-in first-out, every queued tile
-       in every launch.  By default each remedy launch instead processes the
+    /* Tile variant: run the correcting update step and the remedy loop
+       first-in first-out, every queued tile in every launch.  By default each
+       launch instead processes the
        queued tiles whose pending values are lowest (about a thousand, chosen
        by a histogram of per-tile keys) and defers the others, so corrections
        flow roughly in increasing value and fewer nodes are corrected twice.
        Same rules and fixed point either way. */
     EIK_FLAG_FIFO_REMEDY = 16u,
-    /* 3D tile variant: run the update step alone.  By default the persistent
-       workgroups that find no update-step tile in a launch run remedy visits
-       meanwhile (every node of a tile whose update visits left no active
-       node, first-in first-out, stopping when the launch's update visits are
-       done), so corrections start behind the front instead of after the
-       step; the detection pass and remedy loop that follow are unchanged
-       and decide the fixed point (eik_stats.evals_early counts these
-       evaluations). */
+    /* 3D tile variant: run the update step alone, then detection and the
+       remedy.  By default the update step's tile visits already apply the
+       remedy rule (a node whose value drops has its neighbours evaluated
+       again) in increasing value, so corrections start while the front is
+       near instead of after the step; the detection pass that follows checks
+       every node, and the remedy loop takes what it finds (nothing, unless
+       the update step ran out of launches).  eik_stats.evals_early counts
+       the evaluations of tiles visited again (3D float32). */
     EIK_FLAG_NO_EARLY_REMEDY = 32u
 };
 
@@ -129,7 +130,8 @@ typedef struct {
     int64_t written_step2;      /* node values written back to HBM in the update step */
     int64_t written_step3;      /* ... in the remedy loop */
     int64_t evals_check;        /* FIM: evaluations of neighbours of converged nodes */
-    int64_t evals_early;        /* 3D tile variant: remedy evaluations run during the update step */
+    int64_t evals_early;        /* 3D float32 tile variant: remedy evaluations run during the
+                                   update step (revisits of a tile) */
     int64_t kernel_launches[EIK_KERNEL_KINDS]; /* with EIK_FLAG_PROFILE */
     double kernel_ms[EIK_KERNEL_KINDS];        /* with EIK_FLAG_PROFILE: summed device time */
 } eik_stats;
@@ -138,12 +140,9 @@ typedef struct {
     eik_dtype dtype;           /* element type of F / phi (default float32) */
     eik_variant variant;       /* default EIK_VARIANT_TILE */
     int32_t tile[3];           /* tile extents (z, y, x); 0 = library default
-                                  (8^3 in 3D; in 2D 16 x 16, with the update
-                                  step on 32 x 32); an explicit shape applies
-                                  to every step */
+                                  (8^3 in 3D, 16 x 16 in 2D) */
     int32_t inner_iters;       /* tile variant: inner iterations per tile visit; 0 = default:
-                                  4 x the sum of the tile sides, except the
-                                  longest side in the 2D update step */
+                                  4 x the sum of the tile sides */
     int64_t max_iters;         /* cap per loop (0 = default 4 * N + 64) */
     uint32_t flags;            /* EIK_FLAG_* */
     const double* source_values; /* host, n_sources entries; NULL -> all 0 */

@@ -300,9 +300,9 @@ def solve(F, h: Optional[float], sources, eps: float = 0.0, *, variant: Union[st
 
     sources: flat indices, or an (n, ndim) array of coordinates.  Returns phi
     (and a stats dict when stats=True).  fifo=True runs the tile variant's
-    remedy first-in first-out instead of in increasing pending value;
-    early=False keeps the 3D tile variant's idle workgroups out of the update
-    step (no early remedy visits).  async_=True only enqueues (no host
+    visits first-in first-out instead of in increasing pending value;
+    early=False runs the 3D tile variant's update step alone before the
+    remedy (no corrections during it).  async_=True only enqueues (no host
     synchronisation, capturable in a graph): it needs `workspace`, `out` and
     an explicit `max_iters`, and runs exactly max_iters launches per loop."""
     torch = _torch()

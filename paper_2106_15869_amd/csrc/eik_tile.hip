@@ -8,14 +8,18 @@
 // touching HBM, writes back what changed and schedules the tiles that have
 // to be visited next (eik_sched.hpp: sub-list queues, stamps, order keys).
 //
-//   update step (STEP 2): FAR nodes with F > 0 next to a converged or fixed
-//     node become active; active nodes take phi~ = G_i(phi); a node whose
-//     value no longer moves (phi - phi~ <= eps) converges and activates its FAR
+//   update step (STEP 2), default: from the sources outward, tile visits by
+//     the remedy rule below -- a node takes phi~ = G_i(phi) when that is
+//     lower and lists its neighbours -- lowest keys first.  Values settled
+//     from the wrong side are corrected while the front is near (early
+//     remedy) instead of after it has passed.
+//   update step alone (EIK_FLAG_SKIP_REMEDY; 3D with
+//     EIK_FLAG_NO_EARLY_REMEDY): FAR nodes with F > 0 next to a converged or
+//     fixed node become active; active nodes take phi~; a node whose value no
+//     longer moves (phi - phi~ <= eps) converges and activates its FAR
 //     neighbours -- no convergence check of those neighbours (Section 3.3).
 //     A node converging on a tile face schedules the tile across that face; a
-//     tile that still holds active nodes schedules itself.  In 3D the
-//     workgroups that find no update tile in a launch run early remedy
-//     visits (below) on tiles whose update work is done.
+//     tile that still holds active nodes schedules itself.
 //   remedy detection (STEP 3, first part): one dense pass over all tiles;
 //     a tile with any node whose phi~ < phi - eps enters the remedy list.
 //   remedy loop (STEP 3): the remedy rule of Section 3.1.2 restricted to the
@@ -772,8 +776,8 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
 // ---------------------------------------------------------------------------
 // Entry t * NT + n holds the cell value of node n of tile t (H = h / F, or F
 // itself with per-axis spacing; +inf / 0 on a barrier), -1 for a fixed node,
-// the dead value outside the grid.  Built once per solve after the update
-// step: a tile's detection and remedy visits then read one contiguous block
+// the dead value outside the grid.  Built once per solve, after seeding: a
+// tile's detection and visits then read one contiguous block
 // instead of a row of F per cache line and a label byte per node, and do not
 // divide.  (NT is a multiple of 64, so a wave's entries share one tile.)
 template <typename T, int ND, int TX, int TY, int TZ, bool AN>
@@ -874,8 +878,7 @@ TileWs tile_layout(char* base, int64_t n, int64_t ntiles, size_t ninst, size_t i
     return w;
 }
 
-// 2D solves with the default 16 x 16 tiles run the update step on 32 x 32
-// tiles: the update step's launches are bound by the front crossing a tile,
+// The 2D update step alone runs on 32 x 32 tiles by default: its launches are bound by the front crossing a tile,
 // so bigger tiles need fewer of them (2D lognormal 4096^2: update 18.6 ->
 // 17.0 ms), while the remedy is faster on the smaller tiles.
 bool update_tiling(const Batch& b, const eik_options& o, TileCfg& cu) {
