@@ -1115,8 +1115,11 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
             });
             if (e != hipSuccess) return e;
         }
+        // The correcting update step takes every drop: with the tolerance a node
+        // may keep a value up to eps above its solve (64^2 float64 at eps =
+        // 1e-12: 1.3e-15 from the solution instead of 1e-17).
         return timed(prof, phase == 0 ? EIK_KERNEL_UPDATE : EIK_KERNEL_REMEDY,
-                     [&] { return k.remedy(a, geom, eT, inner, gt, s); });
+                     [&] { return k.remedy(a, geom, phase == 0 ? T(0) : eT, inner, gt, s); });
     };
     auto counts = [&](int64_t t) { return w.q.count_of(static_cast<int>(t % 3)); };
 
