@@ -197,11 +197,10 @@ __device__ __forceinline__ T eval_lds(const T* sphi, int L, T v, const Inst<T>& 
 // A remedy visit
 // ---------------------------------------------------------------------------
 // LDS of a remedy visit.
-template <typename T, int NT>
+template <typename T>
 struct RemedyLds {
     T* sphi;           // values with the one-cell halo
-    T* sH;             // the tile's cell values
-    TileLists<NT>* tl;
+    unsigned long long* act;  // three words: chunks changed in an iteration (rotating)
     uint32_t* mask;    // dirty faces the visit starts from
     int* face;         // faces a drop crossed
     int* evals;        // local-solver evaluations
@@ -210,167 +209,153 @@ struct RemedyLds {
     int* written;      // values written back
 };
 
-// The remedy rule on tile t at (x0, y0, z0): stage its values with the halo
-// and its cell values, list the free nodes to recheck (all of them for
-// kAllFaces in the dirty faces, else those on the dirty faces), and iterate
-// until the list is empty or `inner` iterations ran (pending: nodes were
-// still listed).
-// The dirty faces are *s.mask, or lane 0's mask_in when set_mask.  Leaves the
-// new values in sphi with tl->dirty set for the changed nodes, and the
-// crossed faces, evaluations and (ordered) the crossing key in LDS.  Returns
-// the iterations run.
+// The chunks (64 consecutive nodes, one wave's share of a round) that hold a
+// neighbour of a node in the chunks of m, m's own among them.
+template <int ND, int TX, int TY>
+__device__ __forceinline__ unsigned long long chunk_reach(unsigned long long m) {
+    static_assert(64 % TX == 0 || TX % 64 == 0, "a neighbouring row lies in the same or the next chunk");
+    unsigned long long r = m | (m << 1) | (m >> 1);
+    if constexpr (ND == 3) {
+        constexpr int ZS = TX * TY / 64;  // chunks per z slice
+        static_assert(TX * TY % 64 == 0, "z slices are whole chunks");
+        if (ZS > 1) r |= (m << ZS) | (m >> ZS);
+    }
+    return r;
+}
+
+// The remedy rule on tile t at (x0, y0, z0): every lane owns the NPT nodes
+// threadIdx.x + r * kBlock, with their cell values and current values in
+// registers; the values with the halo lie in LDS, where neighbours read them.
+// An iteration evaluates a node per lane and round, takes the drops in place
+// and notes the chunks (64 nodes, one wave) that changed; the next iteration
+// leaves out the chunks none of whose neighbours changed.  Iterations run
+// until nothing changes or `inner` of them ran (pending).  The first one
+// takes the chunks that hold a free node to recheck: any for kAllFaces in the
+// dirty faces, else one on a dirty face.
+// An iteration is one dependent chain (LDS read, solve, LDS write, barrier)
+// of some 500 cycles whatever the number of listed nodes, so evaluating all
+// of a chunk costs no more than its few active nodes: the list of active
+// nodes this replaced (flags claimed and slots reserved by LDS atomics, a
+// list entry read in front of each solve) took three times as long.
+// The dirty faces are *s.mask, or lane 0's mask_in when set_mask.  Writes the
+// changed values back and leaves the crossed faces, counts and (ordered) the
+// crossing key in LDS.  Returns the iterations run.
 template <typename T, int ND, int TX, int TY, int TZ, bool AN>
-__device__ __forceinline__ int remedy_visit(const T* cells, const T* phi, const Inst<T>& g, int t, int x0, int y0,
+__device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T>& g, int t, int x0, int y0,
                                             int z0, int open, T eps, int inner, bool ordered, uint32_t mask_in,
-                                            bool set_mask, const RemedyLds<T, Shape<ND, TX, TY, TZ>::NT>& s,
-                                            bool& pending) {
+                                            bool set_mask, const RemedyLds<T>& s, bool& pending) {
     using S = Shape<ND, TX, TY, TZ>;
+    static_assert(S::NT % kBlock == 0 && S::NT / 64 <= 64, "whole rounds, a chunk per bit");
+    // LDS step from a lane's node of one round to the next
+    constexpr int RSTEP = ND == 2 ? (kBlock / TX) * S::SY : (kBlock / (TX * TY)) * S::SZ;
+    static_assert(kBlock % TX == 0 && (ND == 2 || kBlock % (TX * TY) == 0), "a round is whole rows (slices)");
     const T inf = pos_inf<T>();
-    TileLists<S::NT>& tl = *s.tl;
     T* sphi = s.sphi;
     T hv[S::NPT];
 #pragma unroll
-    for (int r = 0; r < S::NPT; ++r) {
-        const int nn = min(static_cast<int>(threadIdx.x) + r * kBlock, S::NT - 1);
-        hv[r] = cells[static_cast<size_t>(t) * S::NT + nn];
-    }
+    for (int r = 0; r < S::NPT; ++r) hv[r] = cells[static_cast<size_t>(t) * S::NT + threadIdx.x + r * kBlock];
     stage<T, ND, TX, TY, TZ, false, false>(g, x0, y0, z0, phi, nullptr, sphi, nullptr);
-#pragma unroll
-    for (int r = 0; r < S::NPT; ++r) {
-        const int nn = threadIdx.x + r * kBlock;
-        if (nn < S::NT) {
-            s.sH[nn] = hv[r];
-            tl.flag[0][nn] = 0u;
-            tl.flag[1][nn] = 0u;
-            tl.dirty[nn] = 0;
-        }
-    }
     if (threadIdx.x == 0) {
         *s.face = 0;
         *s.evals = 0;
         *s.written = 0;
         *s.unreached = 0;
         if (set_mask) *s.mask = mask_in;
-        tl.cnt[0] = tl.cnt[1] = tl.cnt[2] = 0;
+        s.act[0] = s.act[1] = s.act[2] = 0;
     }
     __syncthreads();
-    // initial remedy list: every non-source node on a first visit, else the
-    // nodes on the faces whose neighbour tile changed (barrier cells and
-    // nodes outside the grid have H = +inf and never change)
     const uint32_t m = *s.mask;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool lane0 = (threadIdx.x & 63) == 0;
+    int nx, ny, nz, L0;
+    node_loc<ND, TX, TY, TZ>(threadIdx.x, nx, ny, nz, L0);
+    T cur[S::NPT], old[S::NPT];
+    int nfree[S::NPT];
+    unsigned long long todo = 0;  // this wave's chunks to evaluate
+    bool unreached = false;
 #pragma unroll
     for (int r = 0; r < S::NPT; ++r) {
-        const int nn = threadIdx.x + r * kBlock;
-        if (nn >= S::NT) continue;
         int x, y, z, L;
-        node_loc<ND, TX, TY, TZ>(nn, x, y, z, L);
+        node_loc<ND, TX, TY, TZ>(threadIdx.x + r * kBlock, x, y, z, L);
         const int E = edge_bits<ND, TX, TY, TZ>(x, y, z) & open;
-        if (!cell_free<T, AN>(s.sH[nn])) continue;
-        if (!(sphi[L] < inf)) *s.unreached = 1;
-        if ((m & kAllFaces) || (E & static_cast<int>(m)))
-            tl.list[0][atomicAdd(&tl.cnt[0], 1)] = static_cast<uint16_t>(nn);
+        cur[r] = old[r] = sphi[L0 + r * RSTEP];
+        const bool fr = cell_free<T, AN>(hv[r]);
+        if (!fr) hv[r] = dead_value<T, AN>();  // solves to +inf: never a drop
+        nfree[r] = __popcll(__ballot(fr));
+        unreached |= fr && !(cur[r] < inf);
+        if (__ballot(fr && ((m & kAllFaces) || (E & static_cast<int>(m))))) todo |= 1ull << (r * (kBlock / 64) + wave);
     }
-    __syncthreads();
+    if (__ballot(unreached) && lane0) *s.unreached = 1;
     pending = false;
-    int my_evals = 0, fm = 0;
-    T kmin = inf;  // smallest value that crossed a face (order key of the pushes)
+    int evals = 0;
     int it = 0;
     for (;; ++it) {
-        const int ncur = tl.cnt[it % 3];
-        if (ncur == 0) break;
+        if (it > 0) {
+            // chunks changed in the previous iteration (uniform)
+            const unsigned long long c = s.act[(it - 1) % 3];
+            const unsigned long long ch =
+                (static_cast<unsigned long long>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(c >> 32))) << 32) |
+                __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(c));
+            if (ch == 0) break;
+            todo = chunk_reach<ND, TX, TY>(ch);
+        }
         if (it == inner) {
             pending = true;
             break;
         }
-        const int cb = it & 1, nb = cb ^ 1;
-        int* ncnt = &tl.cnt[(it + 1) % 3];
-        if (threadIdx.x == 0) tl.cnt[(it + 2) % 3] = 0;
-        for (int i = threadIdx.x; i < ncur; i += kBlock) {
-            const int q = tl.list[cb][i];
-            tl.flag[cb][q] = 0u;
-            int x, y, z, Lq;
-            node_loc<ND, TX, TY, TZ>(q, x, y, z, Lq);
-            ++my_evals;
-            const T hq = s.sH[q];
+        if (threadIdx.x == 0) s.act[(it + 1) % 3] = 0;
+        unsigned long long changed = 0;
+#pragma unroll
+        for (int r = 0; r < S::NPT; ++r) {
+            const unsigned long long bit = 1ull << (r * (kBlock / 64) + wave);
+            if (!(todo & bit)) continue;
+            const int L = L0 + r * RSTEP;
             T nv[2 * ND];
-            load_nb<T, ND, TX, TY, TZ>(sphi, Lq, nv);
-            const T pt = eval_nb<T, ND, AN>(nv, hq, g);
-            // a listed node that may not change (a fixed or barrier node
-            // appended by a neighbour) is skipped here
-            if (cell_free<T, AN>(hq) && pt < sphi[Lq] - eps) {
-                sphi[Lq] = pt;
-                tl.dirty[q] = 1;
-                // the new value reaches the neighbours above it; the values
-                // read for the solve are never below the current ones, so a
-                // neighbour that dropped meanwhile may be listed once more
-                // (an extra evaluation) but none is missed
-                int up = 0;
-#pragma unroll
-                for (int d = 0; d < 2 * ND; ++d) up |= pt < nv[d] ? 1 << d : 0;
-                const int edge = edge_bits<ND, TX, TY, TZ>(x, y, z);
-                if constexpr (ND == 2) {
-                    const int face = up & edge & open;
-                    if (face) {
-                        fm |= face;
-                        kmin = tmin(kmin, pt);
-                    }
-                    // 2D: claim the in-tile neighbours' flags together (an OR
-                    // of 0 on the node's own flag for the other directions
-                    // changes nothing), then reserve a slot per claim won.
-                    // In 3D this was slower (six LDS atomics per changed node
-                    // where about three are needed).
-                    const int in = up & ~edge;
-                    uint32_t prev[2 * ND];
-#pragma unroll
-                    for (int d = 0; d < 2 * ND; ++d) {
-                        const bool c = in & (1 << d);
-                        prev[d] = atomicOr(&tl.flag[nb][c ? q + node_step<TX, TY>(d) : q], c ? 1u : 0u);
-                    }
-#pragma unroll
-                    for (int d = 0; d < 2 * ND; ++d)
-                        if ((in & (1 << d)) && prev[d] == 0u)
-                            tl.list[nb][atomicAdd(ncnt, 1)] = static_cast<uint16_t>(q + node_step<TX, TY>(d));
-                } else {
-#pragma unroll
-                    for (int d = 0; d < 2 * ND; ++d) {
-                        if (!(up & (1 << d))) continue;
-                        if (edge & (1 << d)) {
-                            if (open & (1 << d)) {
-                                fm |= 1 << d;
-                                kmin = tmin(kmin, pt);
-                            }
-                        } else {
-                            list_add(tl, nb, ncnt, q + node_step<TX, TY>(d));
-                        }
-                    }
-                }
+            load_nb<T, ND, TX, TY, TZ>(sphi, L, nv);
+            const T pt = eval_nb<T, ND, AN>(nv, hv[r], g);
+            const bool drop = pt < cur[r] - eps;
+            if (drop) {
+                cur[r] = pt;
+                sphi[L] = pt;
             }
+            if (__ballot(drop)) changed |= bit;
+            evals += nfree[r];
         }
+        if (changed && lane0) atomicOr(&s.act[it % 3], changed);
         __syncthreads();
     }
-    if (fm) atomicOr(s.face, fm);
-    if (my_evals) atomicAdd(s.evals, my_evals);
-    if (ordered && kmin < inf) atomicMin(s.kmin, order_key(kmin));
-    __syncthreads();
-    return it;
-}
-
-// Write back the values a remedy visit changed (and count them).
-template <typename T, int ND, int TX, int TY, int TZ>
-__device__ __forceinline__ void remedy_write_back(T* phi, const Inst<T>& g, int x0, int y0, int z0,
-                                                  const RemedyLds<T, Shape<ND, TX, TY, TZ>::NT>& s) {
-    using S = Shape<ND, TX, TY, TZ>;
-    int my_written = 0;
+    // write back what changed; a changed value that lies below the neighbour
+    // across an open face crosses it
+    int fm = 0, written = 0;
+    T kmin = inf;  // smallest value that crossed a face (order key of the pushes)
 #pragma unroll
     for (int r = 0; r < S::NPT; ++r) {
-        const int nn = threadIdx.x + r * kBlock;
-        if (nn >= S::NT || !s.tl->dirty[nn]) continue;
+        const bool changed = cur[r] < old[r];
+        written += __popcll(__ballot(changed));
+        if (!changed) continue;
         int x, y, z, L;
-        node_loc<ND, TX, TY, TZ>(nn, x, y, z, L);
-        phi[g.node_base + ((z0 + z) * g.ny + (y0 + y)) * g.nx + (x0 + x)] = s.sphi[L];
-        ++my_written;
+        node_loc<ND, TX, TY, TZ>(threadIdx.x + r * kBlock, x, y, z, L);
+        phi[g.node_base + ((z0 + z) * g.ny + (y0 + y)) * g.nx + (x0 + x)] = cur[r];
+        const int E = edge_bits<ND, TX, TY, TZ>(x, y, z) & open;
+        int f = 0;
+#pragma unroll
+        for (int d = 0; d < 2 * ND; ++d)
+            if ((E & (1 << d)) && cur[r] < sphi[L + lds_offset<ND, TX, TY, TZ>(d)]) f |= 1 << d;
+        if (f) {
+            fm |= f;
+            kmin = tmin(kmin, cur[r]);
+        }
     }
-    if (my_written) atomicAdd(s.written, my_written);
+    if (fm) {
+        atomicOr(s.face, fm);
+        if (ordered) atomicMin(s.kmin, order_key(kmin));
+    }
+    if (lane0) {
+        if (evals) atomicAdd(s.evals, evals);
+        if (written) atomicAdd(s.written, written);
+    }
+    __syncthreads();
+    return it;
 }
 
 // ---------------------------------------------------------------------------
@@ -679,8 +664,7 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
     TileIter<T> a, BatchGeom<T> bg, T eps, int inner) {
     using S = Shape<ND, TX, TY, TZ>;
     __shared__ T sphi[S::NL];
-    __shared__ T sH[S::NT];
-    __shared__ TileLists<S::NT> tl;
+    __shared__ unsigned long long s_act[3];
     __shared__ int s_len[kSub];
     __shared__ int s_slot;
     __shared__ int s_face;
@@ -736,13 +720,12 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
             }
             s_kmin = kNoKey;
         }
-        const RemedyLds<T, S::NT> rl{sphi, sH, &tl, &s_mask, &s_face, &s_evals, &s_kmin, &s_unreached, &s_written};
+        const RemedyLds<T> rl{sphi, s_act, &s_mask, &s_face, &s_evals, &s_kmin, &s_unreached, &s_written};
         bool pending;
         const int it = remedy_visit<T, ND, TX, TY, TZ, AN>(a.cells, a.phi, g, t, x0, y0, z0, open, eps, inner,
                                                            a.ordered, mask_in, !from_work, rl, pending);
         // scheduling, one lane per target tile (see the update kernel); the
-        // targets are read by the next launch, so these atomics may overlap
-        // the write-back below
+        // targets are read by the next launch
         if (threadIdx.x < 7) {
             const int d = threadIdx.x;
             const int fmask = s_face;
@@ -758,8 +741,6 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
                 push_keyed(a, tn, ntag, key);
             }
         }
-        remedy_write_back<T, ND, TX, TY, TZ>(a.phi, g, x0, y0, z0, rl);
-        __syncthreads();
         if (threadIdx.x == 0) {
             // a revisit of the merged update step corrects values: early remedy
             (a.early && !s_unreached ? early : evals) += static_cast<unsigned long long>(s_evals);
