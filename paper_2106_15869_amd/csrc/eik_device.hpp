@@ -25,6 +25,57 @@ __device__ __forceinline__ double dev_sqrt(double x) { return __builtin_sqrt(x);
 
 template <typename T> __device__ __forceinline__ T tmin(T a, T b) { return b < a ? b : a; }
 
+// The minimum / maximum instruction itself: fmin() first quiets operands that
+// could be signalling NaNs, one more dependent instruction each.
+__device__ __forceinline__ float vmin(float a, float b) {
+    float r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float vmax(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double vmin(double a, double b) {
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double vmax(double a, double b) {
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// Correctly rounded square root of x = 0, x >= 2^-96 or x = +inf.  The
+// instruction's result s is within one unit u in the last place of the root;
+// as x is a float, the root lies beyond the midpoint of s and s + u exactly if
+// x > s (s + u), and before that of s - u and s if x <= s (s - u); both
+// residuals are signed exactly by a fused multiply-add.  (At 0 and +inf the
+// residuals are 0 or NaN and s stays.)  The library's root also rescales
+// smaller x and tests the class of x, seven more instructions in the chain.
+__device__ __forceinline__ float sqrt_mid(float x) {
+    const float s = __builtin_amdgcn_sqrtf(x);
+    const float dn = __uint_as_float(__float_as_uint(s) - 1u), up = __uint_as_float(__float_as_uint(s) + 1u);
+    const float ed = __builtin_fmaf(-dn, s, x), eu = __builtin_fmaf(-up, s, x);
+    float r = ed <= 0.0f ? dn : s;
+    r = eu > 0.0f ? up : r;
+    return r;
+}
+__device__ __forceinline__ double sqrt_mid(double x) { return dev_sqrt(x); }
+
+// x / 3, correctly rounded (finite x, no underflow): a quotient by the rounded
+// reciprocal, corrected by its exact remainder.
+__device__ __forceinline__ float third(float x) {
+    const float c = 1.0f / 3.0f, q = x * c;
+    return __builtin_fmaf(__builtin_fmaf(-3.0f, q, x), c, q);
+}
+__device__ __forceinline__ double third(double x) {
+    const double c = 1.0 / 3.0, q = x * c;
+    return __builtin_fma(__builtin_fma(-3.0, q, x), c, q);
+}
+
 // Grid extents; 2D grids use nz = 1.  Node count < 2^31.
 struct Grid {
     int nx, ny, nz;
@@ -86,6 +137,45 @@ __device__ __forceinline__ T godunov(T a0, T a1, T a2, T H) {
         phi = phi1 > a1 && phi2 > a2 ? phi3 : phi;
     }
     return H < inf && a0 < inf ? phi : inf;
+}
+
+// Whether godunov_mid may stand in for godunov: H^2 and the discriminants stay
+// clear of the ends of the range (a discriminant that is not 0 is at least
+// 2^-24 H^2: its two terms are of the order of H^2 when they nearly cancel).
+__device__ __forceinline__ bool mid_range(float H) { return H > 0x1p-30f && H < 0x1p+50f; }
+__device__ __forceinline__ bool mid_range(double H) { return H > 0x1p-400 && H < 0x1p+400; }
+
+// godunov for H in the middle of the range (or +inf: the result is +inf or
+// NaN, which is below nothing), the same value bit for bit in a shorter
+// dependent chain, which is what an iteration of a tile visit waits for:
+// minimum instructions, products with powers of two fused into the sums that
+// follow (exact, so rounded once either way), sqrt_mid and third.
+template <typename T, int ND>
+__device__ __forceinline__ T godunov_mid(T a0, T a1, T a2, T H, T HH) {
+    const T lo = vmin(a0, a1), hi = vmax(a0, a1);
+    if (ND == 3) {
+        const T m = vmin(hi, a2);
+        a2 = vmax(hi, a2);
+        a0 = vmin(lo, m);
+        a1 = vmax(lo, m);
+    } else {
+        a0 = lo;
+        a1 = hi;
+    }
+    const T phi1 = a0 + H;
+    const T b = a1 - a0;
+    const T Q = b * b;
+    const T root = sqrt_mid(vmax(__builtin_elementwise_fma(T(-2), Q - HH, Q), T(0)));
+    const T phi2 = __builtin_elementwise_fma(T(0.5), b + root, a0);
+    T phi = phi1 > a1 ? phi2 : phi1;
+    if (ND == 3) {
+        const T c = a2 - a0;
+        const T S = b + c;
+        const T root3 = sqrt_mid(vmax(S * S - T(3) * (Q + c * c - HH), T(0)));
+        const T phi3 = a0 + third(S + root3);
+        phi = phi1 > a1 && phi2 > a2 ? phi3 : phi;
+    }
+    return phi;
 }
 
 // H_i = h / F_i, +inf for a barrier cell.

@@ -35,6 +35,7 @@
 // an update sees either value, both upper bounds of the solution); tiles of
 // one launch see each other's values only through the halo staged at the
 // start of a visit.
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -182,6 +183,16 @@ __device__ __forceinline__ T eval_nb(const T (&nb)[2 * ND], T v, const Inst<T>& 
     return godunov<T, 3>(az, ay, ax, v);
 }
 
+// eval_nb for a node with H in the middle of the range (godunov_mid), equal
+// spacing.
+template <typename T, int ND>
+__device__ __forceinline__ T eval_nb_mid(const T (&nb)[2 * ND], T H, T HH) {
+    const T ax = vmin(nb[0], nb[1]);
+    const T ay = vmin(nb[2], nb[3]);
+    if (ND == 2) return godunov_mid<T, 2>(ay, ax, pos_inf<T>(), H, HH);
+    return godunov_mid<T, 3>(vmin(nb[4], nb[5]), ay, ax, H, HH);
+}
+
 // G_i from the LDS tile (halo holds +inf outside the grid).
 template <typename T, int ND, int TX, int TY, int TZ, bool AN>
 __device__ __forceinline__ T eval_lds(const T* sphi, int L, T v, const Inst<T>& g) {
@@ -197,10 +208,10 @@ __device__ __forceinline__ T eval_lds(const T* sphi, int L, T v, const Inst<T>& 
 // A remedy visit
 // ---------------------------------------------------------------------------
 // LDS of a remedy visit.
-template <typename T>
+template <typename T, typename Mask>
 struct RemedyLds {
     T* sphi;           // values with the one-cell halo
-    unsigned long long* act;  // three words: chunks changed in an iteration (rotating)
+    Mask* act;         // [2][waves]: each wave's chunks that changed in an iteration (by parity)
     uint32_t* mask;    // dirty faces the visit starts from
     int* face;         // faces a drop crossed
     int* evals;        // local-solver evaluations
@@ -209,12 +220,21 @@ struct RemedyLds {
     int* written;      // values written back
 };
 
+// The lanes for which p holds, as a wave-uniform mask.
+__device__ __forceinline__ unsigned long long ballot64(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+
+__device__ __forceinline__ uint32_t first_lane(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ unsigned long long first_lane(unsigned long long v) {
+    return (static_cast<unsigned long long>(first_lane(static_cast<uint32_t>(v >> 32))) << 32) |
+           first_lane(static_cast<uint32_t>(v));
+}
+
 // The chunks (64 consecutive nodes, one wave's share of a round) that hold a
 // neighbour of a node in the chunks of m, m's own among them.
-template <int ND, int TX, int TY>
-__device__ __forceinline__ unsigned long long chunk_reach(unsigned long long m) {
+template <int ND, int TX, int TY, typename Mask>
+__device__ __forceinline__ Mask chunk_reach(Mask m) {
     static_assert(64 % TX == 0 || TX % 64 == 0, "a neighbouring row lies in the same or the next chunk");
-    unsigned long long r = m | (m << 1) | (m >> 1);
+    Mask r = m | (m << 1) | (m >> 1);
     if constexpr (ND == 3) {
         constexpr int ZS = TX * TY / 64;  // chunks per z slice
         static_assert(TX * TY % 64 == 0, "z slices are whole chunks");
@@ -233,19 +253,23 @@ __device__ __forceinline__ unsigned long long chunk_reach(unsigned long long m) 
 // takes the chunks that hold a free node to recheck: any for kAllFaces in the
 // dirty faces, else one on a dirty face.
 // An iteration is one dependent chain (LDS read, solve, LDS write, barrier)
-// of some 500 cycles whatever the number of listed nodes, so evaluating all
-// of a chunk costs no more than its few active nodes: the list of active
-// nodes this replaced (flags claimed and slots reserved by LDS atomics, a
-// list entry read in front of each solve) took three times as long.
+// whatever the number of active nodes, so evaluating all of a chunk costs no
+// more than its few active nodes.  2D lognormal 4096^2: 28.5 ms with an LDS
+// list of active nodes (flags and slots claimed by LDS atomics around each
+// solve), 17.9 ms with dense rounds at 1000 cycles an iteration, 14.4 ms with
+// the chain shortened (godunov_mid, neighbours and masks read in one LDS
+// round, a mask word per wave instead of an atomic); maze 256^3 9.07, 6.27,
+// 5.03 ms.
 // The dirty faces are *s.mask, or lane 0's mask_in when set_mask.  Writes the
 // changed values back and leaves the crossed faces, counts and (ordered) the
 // crossing key in LDS.  Returns the iterations run.
-template <typename T, int ND, int TX, int TY, int TZ, bool AN>
+template <typename T, int ND, int TX, int TY, int TZ, bool AN, typename Mask>
 __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T>& g, int t, int x0, int y0,
                                             int z0, int open, T eps, int inner, bool ordered, uint32_t mask_in,
-                                            bool set_mask, const RemedyLds<T>& s, bool& pending) {
+                                            bool set_mask, const RemedyLds<T, Mask>& s, bool& pending) {
     using S = Shape<ND, TX, TY, TZ>;
-    static_assert(S::NT % kBlock == 0 && S::NT / 64 <= 64, "whole rounds, a chunk per bit");
+    constexpr int WAVES = kBlock / 64;
+    static_assert(S::NT % kBlock == 0 && S::NT / 64 <= 8 * sizeof(Mask), "whole rounds, a chunk per bit");
     // LDS step from a lane's node of one round to the next
     constexpr int RSTEP = ND == 2 ? (kBlock / TX) * S::SY : (kBlock / (TX * TY)) * S::SZ;
     static_assert(kBlock % TX == 0 && (ND == 2 || kBlock % (TX * TY) == 0), "a round is whole rows (slices)");
@@ -261,7 +285,6 @@ __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T
         *s.written = 0;
         *s.unreached = 0;
         if (set_mask) *s.mask = mask_in;
-        s.act[0] = s.act[1] = s.act[2] = 0;
     }
     __syncthreads();
     const uint32_t m = *s.mask;
@@ -269,10 +292,10 @@ __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T
     const bool lane0 = (threadIdx.x & 63) == 0;
     int nx, ny, nz, L0;
     node_loc<ND, TX, TY, TZ>(threadIdx.x, nx, ny, nz, L0);
-    T cur[S::NPT], old[S::NPT];
+    T cur[S::NPT], old[S::NPT], hh[S::NPT];
     int nfree[S::NPT];
-    unsigned long long todo = 0;  // this wave's chunks to evaluate
-    bool unreached = false;
+    Mask todo = 0;  // chunks to evaluate (the wave looks at its own)
+    bool unreached = false, ends = false;
 #pragma unroll
     for (int r = 0; r < S::NPT; ++r) {
         int x, y, z, L;
@@ -280,50 +303,75 @@ __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T
         const int E = edge_bits<ND, TX, TY, TZ>(x, y, z) & open;
         cur[r] = old[r] = sphi[L0 + r * RSTEP];
         const bool fr = cell_free<T, AN>(hv[r]);
-        if (!fr) hv[r] = dead_value<T, AN>();  // solves to +inf: never a drop
-        nfree[r] = __popcll(__ballot(fr));
+        if (!fr) hv[r] = dead_value<T, AN>();  // never solves to a drop
+        hh[r] = hv[r] * hv[r];
+        nfree[r] = __popcll(ballot64(fr));
         unreached |= fr && !(cur[r] < inf);
-        if (__ballot(fr && ((m & kAllFaces) || (E & static_cast<int>(m))))) todo |= 1ull << (r * (kBlock / 64) + wave);
+        ends |= fr && !mid_range(hv[r]);
+        if (ballot64(fr && ((m & kAllFaces) || (E & static_cast<int>(m))))) todo |= Mask(1) << (r * WAVES + wave);
     }
-    if (__ballot(unreached) && lane0) *s.unreached = 1;
+    if (ballot64(unreached) && lane0) *s.unreached = 1;
     pending = false;
     int evals = 0;
     int it = 0;
-    for (;; ++it) {
-        if (it > 0) {
-            // chunks changed in the previous iteration (uniform)
-            const unsigned long long c = s.act[(it - 1) % 3];
-            const unsigned long long ch =
-                (static_cast<unsigned long long>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(c >> 32))) << 32) |
-                __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(c));
-            if (ch == 0) break;
-            todo = chunk_reach<ND, TX, TY>(ch);
-        }
-        if (it == inner) {
-            pending = true;
-            break;
-        }
-        if (threadIdx.x == 0) s.act[(it + 1) % 3] = 0;
-        unsigned long long changed = 0;
+    // (a loop for each of the two local solves: in one loop the compiler moves
+    // parts of both in front of the choice)
+    auto iterate = [&](auto mid_c) __attribute__((always_inline)) {
+        for (;; ++it) {
+            // chunks changed in the previous iteration, and for tiles of one
+            // or two nodes per lane every neighbour value in the same LDS round
+            // (the empty asm keeps the loads out of the branches that use them)
+            constexpr bool AHEAD = S::NPT <= 2;
+            T nv[AHEAD ? S::NPT : 1][2 * ND];
+            Mask act[WAVES] = {};
+            if (it > 0) {
 #pragma unroll
-        for (int r = 0; r < S::NPT; ++r) {
-            const unsigned long long bit = 1ull << (r * (kBlock / 64) + wave);
-            if (!(todo & bit)) continue;
-            const int L = L0 + r * RSTEP;
-            T nv[2 * ND];
-            load_nb<T, ND, TX, TY, TZ>(sphi, L, nv);
-            const T pt = eval_nb<T, ND, AN>(nv, hv[r], g);
-            const bool drop = pt < cur[r] - eps;
-            if (drop) {
-                cur[r] = pt;
-                sphi[L] = pt;
+                for (int w = 0; w < WAVES; ++w) act[w] = s.act[((it - 1) & 1) * WAVES + w];
             }
-            if (__ballot(drop)) changed |= bit;
-            evals += nfree[r];
+            if (AHEAD) {
+#pragma unroll
+                for (int r = 0; r < S::NPT; ++r) {
+                    load_nb<T, ND, TX, TY, TZ>(sphi, L0 + r * RSTEP, nv[AHEAD ? r : 0]);
+#pragma unroll
+                    for (int d = 0; d < 2 * ND; ++d) asm volatile("" : "+v"(nv[AHEAD ? r : 0][d]));
+                }
+            }
+            if (it > 0) {
+                Mask ch = 0;
+#pragma unroll
+                for (int w = 0; w < WAVES; ++w) ch |= act[w];
+                ch = first_lane(ch);
+                if (ch == 0) break;
+                todo = chunk_reach<ND, TX, TY>(ch);
+            }
+            if (it == inner) {
+                pending = true;
+                break;
+            }
+            Mask changed = 0;
+    #pragma unroll
+            for (int r = 0; r < S::NPT; ++r) {
+                const Mask bit = Mask(1) << (r * WAVES + wave);
+                if (!(todo & bit)) continue;
+                const int L = L0 + r * RSTEP;
+                T(&v)[2 * ND] = nv[AHEAD ? r : 0];
+                if (!AHEAD) load_nb<T, ND, TX, TY, TZ>(sphi, L, v);
+                T pt;
+                if constexpr (decltype(mid_c)::value) pt = eval_nb_mid<T, ND>(v, hv[r], hh[r]);
+                else pt = eval_nb<T, ND, AN>(v, hv[r], g);
+                const bool drop = pt < cur[r] - eps;
+                cur[r] = drop ? pt : cur[r];
+                sphi[L] = cur[r];  // (only this lane writes it)
+                if (ballot64(drop)) changed |= bit;
+                evals += nfree[r];
+            }
+            if (lane0) s.act[(it & 1) * WAVES + wave] = changed;
+            __syncthreads();
         }
-        if (changed && lane0) atomicOr(&s.act[it % 3], changed);
-        __syncthreads();
-    }
+    };
+    if constexpr (AN) iterate(std::false_type{});
+    else if (ballot64(ends) == 0) iterate(std::true_type{});
+    else iterate(std::false_type{});
     // write back what changed; a changed value that lies below the neighbour
     // across an open face crosses it
     int fm = 0, written = 0;
@@ -331,7 +379,7 @@ __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T
 #pragma unroll
     for (int r = 0; r < S::NPT; ++r) {
         const bool changed = cur[r] < old[r];
-        written += __popcll(__ballot(changed));
+        written += __popcll(ballot64(changed));
         if (!changed) continue;
         int x, y, z, L;
         node_loc<ND, TX, TY, TZ>(threadIdx.x + r * kBlock, x, y, z, L);
@@ -664,7 +712,8 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
     TileIter<T> a, BatchGeom<T> bg, T eps, int inner) {
     using S = Shape<ND, TX, TY, TZ>;
     __shared__ T sphi[S::NL];
-    __shared__ unsigned long long s_act[3];
+    using Mask = std::conditional_t<(S::NT <= 32 * 64), uint32_t, unsigned long long>;  // a bit per chunk
+    __shared__ Mask s_act[2 * kBlock / 64];
     __shared__ int s_len[kSub];
     __shared__ int s_slot;
     __shared__ int s_face;
@@ -720,7 +769,7 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
             }
             s_kmin = kNoKey;
         }
-        const RemedyLds<T> rl{sphi, s_act, &s_mask, &s_face, &s_evals, &s_kmin, &s_unreached, &s_written};
+        const RemedyLds<T, Mask> rl{sphi, s_act, &s_mask, &s_face, &s_evals, &s_kmin, &s_unreached, &s_written};
         bool pending;
         const int it = remedy_visit<T, ND, TX, TY, TZ, AN>(a.cells, a.phi, g, t, x0, y0, z0, open, eps, inner,
                                                            a.ordered, mask_in, !from_work, rl, pending);

@@ -1,0 +1,47 @@
+"""The two local solves of a tile visit: nodes whose H = h / F lies in the
+middle of the range take the short one, others the general one.  Scaling h by
+a power of two scales every operation's result by it exactly, so the two have
+to agree bit for bit, on every tile shape; and both agree with the oracle."""
+
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _field(dims, seed):
+    rng = np.random.default_rng(seed)
+    F = rng.uniform(0.2, 3.0, size=dims)
+    F[rng.random(dims) < 0.05] = 0.0  # barriers
+    F.reshape(-1)[0] = 1.0
+    return F
+
+
+@pytest.mark.parametrize("dims,tile", [
+    ((37, 50), None), ((37, 50), (32, 32)), ((37, 50), (16, 64)), ((37, 50), (8, 32)), ((130, 70), (64, 64)),
+    ((1, 33), None), ((16, 16), None),
+    ((19, 13, 21), None), ((19, 13, 21), (4, 8, 8)), ((19, 13, 21), (4, 4, 16)), ((19, 13, 21), (8, 8, 16)),
+    ((19, 33, 21), (16, 16, 16)), ((8, 8, 8), None),
+])
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+def test_short_and_general_solve_agree(dims, tile, dtype):
+    import paper_2106_15869_amd as eik
+    F = _field(dims, 5).astype(dtype)
+    src = np.array([0], dtype=np.int64)
+    Fd = torch.from_numpy(F).cuda()
+    mid = eik.solve(Fd, 0.25, src, tile=tile).cpu().numpy()
+    shift = 2.0 ** (40 if dtype == "float32" else 450)
+    for k in (shift, 1.0 / shift):
+        other = eik.solve(Fd, 0.25 * k, src, tile=tile).cpu().numpy()
+        np.testing.assert_array_equal(other, (mid * np.array(k, dtype=dtype)).astype(dtype))
+    ref = oracle.fmm(F.astype(np.float64), 0.25, src)
+    live = np.isfinite(ref)
+    np.testing.assert_array_equal(live, np.isfinite(mid))
+    # a value is the end of a chain of at most sum(dims) local solves, each
+    # within a few units in the last place
+    tol = 8 * sum(dims) * np.finfo(dtype).eps
+    np.testing.assert_allclose(mid[live], ref[live], rtol=tol)
