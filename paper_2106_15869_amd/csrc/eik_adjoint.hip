@@ -8,17 +8,23 @@
 //     lambda = dL/dphi + M^T lambda,
 // a triangular system in causal order.
 //
-//   k_adj_prep   per node, tile by tile: the upwind neighbour on each axis
-//                (lower index on a tie), the weights c_ik = w_ik / W_i, D_i.
+//   k_adj_prep   tile by tile: the upwind neighbour on each axis (lower index
+//                on a tie), the weights c_ik = w_ik / W_i and D_i; written as
+//                what the recurrence pulls, tile-major: for node j and
+//                direction d the weight on j of its neighbour there, 0 where j
+//                is not upwind of it.  Tiles holding a nonzero dL/dphi are
+//                queued.
 //   Grids of a batch are tiled back to back (see eik_tile.hpp); every kernel
 //   looks up the instance of the tile it works on.
 //   k_adj_tile   tile work queues (eik_sched.hpp): a persistent workgroup
-//                stages lambda and the stencil data of a tile plus halo in
-//                LDS and recomputes
-//                lambda_j = g_j + sum_{i : j upwind of i} c_{i,axis} lambda_i
-//                over an LDS list: a node whose lambda changes lists the
-//                nodes upwind of it (they pull from it); across a tile face it
-//                marks that face dirty in the neighbour tile and queues it.
+//                stages lambda of a tile plus halo in LDS, the pulled weights
+//                in registers, and recomputes
+//                lambda_j = g_j + sum_d pull_jd lambda_{j+d}
+//                in dense rounds (see remedy_visit in eik_tile.hip; 900 x 1100
+//                4.4 -> 1.8 ms, 192^3 3.6 -> 1.8 ms against an LDS list of
+//                nodes and weights staged as stored) until nothing changes; a node on a tile face whose upwind neighbour
+//                lies across it marks that face dirty in the neighbour tile
+//                and queues it.
 //                lambda starts at 0 and the tiles holding a nonzero dL/dphi
 //                start queued, so every node with g_j != 0 changes on its
 //                first evaluation and passes its value on, also across a face.
@@ -41,59 +47,83 @@ namespace eik {
 
 namespace {
 
-constexpr uint8_t kSrc = 0x80u;   // stencil byte: node is a source
-// stencil byte bits: axis k present -> bit 2k; upwind on the + side -> bit 2k+1
-// (axis 0 = x, 1 = y, 2 = z)
+// stencil byte: bit d set if the node's upwind neighbour on the axis of
+// direction d (-x, +x, -y, +y, -z, +z) lies there; 0 for sources, barriers and
+// unreached nodes
 
 template <typename T>
 struct AdjIter : Sched {
     const T* phi;
     const T* g;      // dL/dphi
     T* lam;
-    const uint8_t* up;  // stencil bytes
-    const T* coef;      // 3 per node (x, y, z)
+    const uint8_t* up;  // stencil bytes, tile-major
+    const T* pull;      // pulled weights, tile-major: [tile][direction][node]
 };
 
 // ---------------------------------------------------------------------------
+// One workgroup per tile: phi with a halo of two nodes in LDS, from it the
+// stencil of the tile's nodes and of a halo of one, from that the weights each
+// node pulls.  Also lambda = 0 and the initial list: tiles holding a nonzero
+// dL/dphi (all nodes to recompute), keyed by the largest arrival time among
+// those nodes.  Written once, the pulled weights spare every visit the staging
+// of three weights and a stencil byte per node and halo node (13 bytes each,
+// at a stride of 12).
 template <typename T, int ND, int TX, int TY, int TZ>
-__global__ __launch_bounds__(kBlock) void k_adj_prep(BatchGeom<T> bg, const T* __restrict__ F,
-                                                     const T* __restrict__ phi, uint8_t* up, T* coef, T* D,
-                                                     T* lam, const T* __restrict__ g) {
-    constexpr int NT = TX * TY * (ND == 3 ? TZ : 1);
+__global__ __launch_bounds__(kBlock) void k_adj_prep(AdjIter<T> a, BatchGeom<T> bg, const T* __restrict__ F, uint8_t* up,
+                                                     T* pull, T* D) {
+    using S = Shape<ND, TX, TY, TZ>;
+    constexpr int PX = TX + 4, PY = TY + 4, PZ = ND == 3 ? TZ + 4 : 1, PN = PX * PY * PZ;
+    __shared__ T sphi[PN];
+    __shared__ T sw[ND][S::NL];      // weights by axis (x, y, z)
+    __shared__ uint8_t sup[S::NL];   // stencil bytes
+    __shared__ uint32_t s_key;
     const T inf = pos_inf<T>();
     for (int t = blockIdx.x; t < bg.ntiles; t += gridDim.x) {
         const Inst<T> I = inst_of(bg, t);
         const int lt = t - I.tile_base;
         const int x0 = (lt % I.ntx) * TX, y0 = ((lt / I.ntx) % I.nty) * TY;
         const int z0 = ND == 3 ? (lt / (I.ntx * I.nty)) * TZ : 0;
-        for (int q = threadIdx.x; q < NT; q += kBlock) {
-            const int x = x0 + q % TX, y = y0 + (q / TX) % TY, z = ND == 3 ? z0 + q / (TX * TY) : 0;
-            if (x >= I.nx || y >= I.ny || z >= I.nz) continue;
-            const int sy = I.nx, sz = I.nx * I.ny;
-            const int i = I.node_base + (z * I.ny + y) * I.nx + x;
-            const T p = phi[i];
-            const T f = F[i];
+        auto node = [&](int x, int y, int z) {
+            const int cx = min(max(x, 0), I.nx - 1), cy = min(max(y, 0), I.ny - 1), cz = min(max(z, 0), I.nz - 1);
+            return I.node_base + (cz * I.ny + cy) * I.nx + cx;
+        };
+        auto inside = [&](int x, int y, int z) {
+            return x >= 0 && x < I.nx && y >= 0 && y < I.ny && z >= 0 && z < I.nz;
+        };
+        if (threadIdx.x == 0) s_key = kNoKey;
+        for (int q = threadIdx.x; q < PN; q += kBlock) {
+            const int x = x0 + q % PX - 2, y = y0 + (q / PX) % PY - 2, z = ND == 3 ? z0 + q / (PX * PY) - 2 : 0;
+            const T p = a.phi[node(x, y, z)];
+            sphi[q] = inside(x, y, z) ? p : inf;
+        }
+        __syncthreads();
+        for (int q = threadIdx.x; q < S::NL; q += kBlock) {
+            const int lx = q % S::LX, ly = (q / S::LX) % S::LY, lz = ND == 3 ? q / (S::LX * S::LY) : 0;
+            const int x = x0 + lx - 1, y = y0 + ly - 1, z = ND == 3 ? z0 + lz - 1 : 0;
+            const int c = ((ND == 3 ? lz + 1 : 0) * PY + ly + 1) * PX + lx + 1;
+            const bool ok = inside(x, y, z);
+            const T f = F[node(x, y, z)];
+            const T p = sphi[c];
             uint8_t u = 0;
             T w[3] = {T(0), T(0), T(0)};
             T W = T(0);
-            if (p < inf && f > T(0)) {
-                const int st[3] = {1, sy, sz};
-                const int cc[3] = {x, y, z};
-                const int dd[3] = {I.nx, I.ny, I.nz};
+            if (ok && p < inf && f > T(0)) {
+                constexpr int st[3] = {1, PX, PX * PY};
 #pragma unroll
                 for (int k = 0; k < ND; ++k) {
+                    const T lo = sphi[c - st[k]], hi = sphi[c + st[k]];  // +inf outside the grid
                     T v = inf;
                     int side = -1;
-                    if (cc[k] > 0 && phi[i - st[k]] < v) {
-                        v = phi[i - st[k]];
+                    if (lo < v) {
+                        v = lo;
                         side = 0;
                     }
-                    if (cc[k] + 1 < dd[k] && phi[i + st[k]] < v) {
-                        v = phi[i + st[k]];
+                    if (hi < v) {
+                        v = hi;
                         side = 1;
                     }
                     if (side >= 0 && v < p) {
-                        u |= static_cast<uint8_t>((1u << (2 * k)) | (static_cast<uint32_t>(side) << (2 * k + 1)));
+                        u |= static_cast<uint8_t>(1u << (2 * k + side));
                         // per-axis spacing weighs axis k by 1 / spacing^2 (axis k = x, y, z
                         // is dims entry ND - 1 - k)
                         const T dk = I.d[ND - 1 - k];
@@ -111,62 +141,38 @@ __global__ __launch_bounds__(kBlock) void k_adj_prep(BatchGeom<T> bg, const T* _
                     d = -(Hh * Hh) / (f * W);
                 }
 #pragma unroll
-                for (int k = 0; k < 3; ++k) w[k] = w[k] / W;
+                for (int k = 0; k < ND; ++k) w[k] = w[k] / W;
             } else {
                 u = 0;
-                w[0] = w[1] = w[2] = T(0);
+#pragma unroll
+                for (int k = 0; k < ND; ++k) w[k] = T(0);
             }
-            up[i] = u;
-            coef[3 * static_cast<size_t>(i) + 0] = w[0];
-            coef[3 * static_cast<size_t>(i) + 1] = w[1];
-            coef[3 * static_cast<size_t>(i) + 2] = w[2];
-            D[i] = d;
-            lam[i] = T(0);
+            sup[q] = u;
+#pragma unroll
+            for (int k = 0; k < ND; ++k) sw[k][q] = w[k];
+            const bool owned = lx >= 1 && lx <= TX && ly >= 1 && ly <= TY && (ND == 2 || (lz >= 1 && lz <= TZ));
+            if (ok && owned) D[node(x, y, z)] = d;
         }
-    }
-}
-
-template <typename T>
-__global__ void k_adj_mark_sources(SrcBatch<T> b, uint8_t* up, T* coef, T* D) {
-    const int k = threadIdx.x;
-    if (k >= b.count) return;
-    const int i = b.idx[k];
-    up[i] = kSrc;
-    coef[3 * static_cast<size_t>(i) + 0] = T(0);
-    coef[3 * static_cast<size_t>(i) + 1] = T(0);
-    coef[3 * static_cast<size_t>(i) + 2] = T(0);
-    D[i] = T(0);
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_adj_final(int n, const T* __restrict__ D,
-                                                      const T* __restrict__ lam, T* __restrict__ out) {
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) out[i] = D[i] * lam[i];
-}
-
-// ---------------------------------------------------------------------------
-// Initial list: tiles holding a nonzero dL/dphi (all nodes to recompute),
-// keyed by the largest arrival time among those nodes.
-template <typename T, int ND, int TX, int TY, int TZ>
-__global__ __launch_bounds__(kBlock) void k_adj_seed(AdjIter<T> a, BatchGeom<T> bg) {
-    using S = Shape<ND, TX, TY, TZ>;
-    __shared__ uint32_t s_key;
-    for (int t = blockIdx.x; t < bg.ntiles; t += gridDim.x) {
-        const Inst<T> g = inst_of(bg, t);
-        const int lt = t - g.tile_base;
-        const int tx = lt % g.ntx, ty = (lt / g.ntx) % g.nty, tz = lt / (g.ntx * g.nty);
-        if (threadIdx.x == 0) s_key = kNoKey;
         __syncthreads();
         bool nz = false;
-        for (int q = threadIdx.x; q < S::NT; q += kBlock) {
-            const int x = tx * TX + q % TX, y = ty * TY + (q / TX) % TY;
-            const int z = ND == 3 ? tz * TZ + q / (TX * TY) : 0;
-            if (x < g.nx && y < g.ny && z < g.nz) {
-                const int i = g.node_base + (z * g.ny + y) * g.nx + x;
-                if (a.g[i] != T(0)) {
-                    nz = true;
-                    atomicMin(&s_key, order_key(-a.phi[i]));
-                }
+        for (int n = threadIdx.x; n < S::NT; n += kBlock) {
+            int x, y, z, L;
+            node_loc<ND, TX, TY, TZ>(n, x, y, z, L);
+            const size_t e = static_cast<size_t>(t) * S::NT;
+            up[e + n] = sup[L];
+#pragma unroll
+            for (int d = 0; d < 2 * ND; ++d) {
+                // the neighbour in direction d pushes to this node if its upwind
+                // neighbour on that axis lies in the opposite direction
+                const int p = L + lds_offset<ND, TX, TY, TZ>(d);
+                pull[e * (2 * ND) + d * S::NT + n] = (sup[p] >> (d ^ 1)) & 1u ? sw[d >> 1][p] : T(0);
+            }
+            if (!inside(x0 + x, y0 + y, z0 + z)) continue;
+            const int i = node(x0 + x, y0 + y, z0 + z);
+            a.lam[i] = T(0);
+            if (a.g[i] != T(0)) {
+                nz = true;
+                atomicMin(&s_key, order_key(-a.phi[i]));
             }
         }
         if (__syncthreads_or(nz) && threadIdx.x == 0) {
@@ -175,6 +181,40 @@ __global__ __launch_bounds__(kBlock) void k_adj_seed(AdjIter<T> a, BatchGeom<T> 
         }
         __syncthreads();
     }
+}
+
+// A source has no stencil: nothing pulls from it, and it has no gradient.
+template <typename T, int ND, int TX, int TY, int TZ>
+__global__ void k_adj_mark_sources(BatchGeom<T> bg, SrcBatch<T> b, uint8_t* up, T* pull, T* D) {
+    using S = Shape<ND, TX, TY, TZ>;
+    const int k = threadIdx.x;
+    if (k >= b.count) return;
+    const Inst<T> g = bg.ninst == 1 ? bg.one : bg.table[b.inst[k]];
+    const int i = b.idx[k] - g.node_base;
+    const int x = i % g.nx, y = (i / g.nx) % g.ny, z = i / (g.nx * g.ny);
+    D[b.idx[k]] = T(0);
+    auto entry = [&](int X, int Y, int Z, size_t& e, int& n) {
+        const int t = g.tile_base + ((Z / (ND == 3 ? TZ : 1)) * g.nty + Y / TY) * g.ntx + X / TX;
+        e = static_cast<size_t>(t) * S::NT;
+        n = ((ND == 3 ? Z % TZ : 0) * TY + Y % TY) * TX + X % TX;
+    };
+    size_t e;
+    int n;
+    entry(x, y, z, e, n);
+    up[e + n] = 0;
+    constexpr int dx[6] = {-1, 1, 0, 0, 0, 0}, dy[6] = {0, 0, -1, 1, 0, 0}, dz[6] = {0, 0, 0, 0, -1, 1};
+    for (int d = 0; d < 2 * ND; ++d) {
+        const int X = x + dx[d], Y = y + dy[d], Z = z + dz[d];
+        if (X < 0 || X >= g.nx || Y < 0 || Y >= g.ny || Z < 0 || Z >= g.nz) continue;
+        entry(X, Y, Z, e, n);
+        pull[e * (2 * ND) + (d ^ 1) * S::NT + n] = T(0);  // seen from there the source lies the other way
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_adj_final(int n, const T* __restrict__ D,
+                                                      const T* __restrict__ lam, T* __restrict__ out) {
+    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) out[i] = D[i] * lam[i];
 }
 
 // Resident workgroups per CU: six for 8^3 float tiles, so that all 1536
@@ -188,11 +228,15 @@ template <typename T, int ND, int TX, int TY, int TZ>
 __global__ __launch_bounds__(kBlock, (adj_blocks_per_cu<ND, Shape<ND, TX, TY, TZ>::NPT, T>())) void k_adj_tile(
     AdjIter<T> a, BatchGeom<T> bg, int inner) {
     using S = Shape<ND, TX, TY, TZ>;
+    using Mask = ChunkMask<S::NT>;
+    constexpr int WAVES = kBlock / 64;
+    // LDS step from a lane's node of one round to the next
+    constexpr int RSTEP = ND == 2 ? (kBlock / TX) * S::SY : (kBlock / (TX * TY)) * S::SZ;
+    static_assert(S::NT % kBlock == 0 && kBlock % TX == 0 && (ND == 2 || kBlock % (TX * TY) == 0),
+                  "whole rounds of whole rows (slices)");
+    static_assert(S::NPT <= 2, "a lane holds every neighbour value of its nodes");
     __shared__ T slam[S::NL];
-    __shared__ T scoef[3 * S::NL];
-    __shared__ uint8_t sup[S::NL];
-    __shared__ T sg[S::NT];
-    __shared__ TileLists<S::NT> tl;
+    __shared__ Mask s_act[2 * WAVES];  // each wave's chunks that changed in an iteration (by parity)
     __shared__ int s_len[kSub];
     __shared__ int s_slot;
     __shared__ int s_face;
@@ -207,7 +251,10 @@ __global__ __launch_bounds__(kBlock, (adj_blocks_per_cu<ND, Shape<ND, TX, TY, TZ
     const TList src = from_work ? a.work : a.cur;
     const int k = blockIdx.x & (kSub - 1);
     const int len = from_work ? s_wlen[k] : s_len[k];
-    constexpr int SY = S::LX, SZ = S::LX * S::LY;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool lane0 = (threadIdx.x & 63) == 0;
+    int nx_, ny_, nz_, L0;
+    node_loc<ND, TX, TY, TZ>(threadIdx.x, nx_, ny_, nz_, L0);
     unsigned long long visits = 0;
     for (bool first = true;; first = false) {
         if (threadIdx.x == 0) {
@@ -230,7 +277,6 @@ __global__ __launch_bounds__(kBlock, (adj_blocks_per_cu<ND, Shape<ND, TX, TY, TZ
             }
             s_kmin = kNoKey;
             s_face = 0;
-            tl.cnt[0] = tl.cnt[1] = tl.cnt[2] = 0;
             s_slot = tt;
         }
         __syncthreads();
@@ -242,15 +288,18 @@ __global__ __launch_bounds__(kBlock, (adj_blocks_per_cu<ND, Shape<ND, TX, TY, TZ
         const int tx = lt % g.ntx, ty = (lt / g.ntx) % g.nty, tz = lt / (g.ntx * g.nty);
         const int x0 = tx * TX, y0 = ty * TY, z0 = tz * (ND == 3 ? TZ : 1);
         const int open = open_bits<ND, TX, TY, TZ>(g, x0, y0, z0);
-        // stage lambda, stencil bytes and coefficients with the halo (0 outside)
-        // and dL/dphi of the tile's nodes: addresses are clamped into the grid
-        // so every global load of a lane is issued before its first LDS store
+        // lambda with the halo (0 outside) to LDS; the nodes' pulled weights,
+        // dL/dphi, stencil bytes and (on open faces) arrival times to
+        // registers: addresses are clamped into the grid so every global load
+        // of a lane is issued before its first LDS store
+        T c[S::NPT][2 * ND], gv[S::NPT], ph[S::NPT], cur[S::NPT], old[S::NPT];
+        uint32_t u[S::NPT];
+        bool ok[S::NPT];
+        int G[S::NPT], E[S::NPT];
         {
             constexpr int NIT = (S::NL + kBlock - 1) / kBlock;
-            constexpr int NPT = (S::NT + kBlock - 1) / kBlock;
-            T vl[NIT], c0[NIT], c1[NIT], c2[NIT], vg[NPT];
-            uint8_t vu[NIT];
-            bool in[NIT], okn[NPT];
+            T vl[NIT];
+            bool in[NIT];
 #pragma unroll
             for (int j = 0; j < NIT; ++j) {
                 const int q = min(static_cast<int>(threadIdx.x) + j * kBlock, S::NL - 1);
@@ -259,122 +308,98 @@ __global__ __launch_bounds__(kBlock, (adj_blocks_per_cu<ND, Shape<ND, TX, TY, TZ
                 in[j] = gx >= 0 && gx < g.nx && gy >= 0 && gy < g.ny && gz >= 0 && gz < g.nz;
                 const int cx = min(max(gx, 0), g.nx - 1), cy = min(max(gy, 0), g.ny - 1);
                 const int cz = min(max(gz, 0), g.nz - 1);
-                const size_t G = static_cast<size_t>(g.node_base) + (cz * g.ny + cy) * g.nx + cx;
-                vl[j] = a.lam[G];
-                vu[j] = a.up[G];
-                c0[j] = a.coef[3 * G + 0];
-                c1[j] = a.coef[3 * G + 1];
-                c2[j] = a.coef[3 * G + 2];
+                vl[j] = a.lam[g.node_base + (cz * g.ny + cy) * g.nx + cx];
             }
+            const size_t e = static_cast<size_t>(t) * S::NT;
 #pragma unroll
-            for (int r = 0; r < NPT; ++r) {
-                const int nn = min(static_cast<int>(threadIdx.x) + r * kBlock, S::NT - 1);
+            for (int r = 0; r < S::NPT; ++r) {
+                const int nn = threadIdx.x + r * kBlock;
                 int x, y, z, L;
                 node_loc<ND, TX, TY, TZ>(nn, x, y, z, L);
-                okn[r] = x0 + x < g.nx && y0 + y < g.ny && z0 + z < g.nz;
-                const int cx = min(x0 + x, g.nx - 1), cy = min(y0 + y, g.ny - 1), cz = min(z0 + z, g.nz - 1);
-                vg[r] = a.g[g.node_base + (cz * g.ny + cy) * g.nx + cx];
+                ok[r] = x0 + x < g.nx && y0 + y < g.ny && z0 + z < g.nz;
+                E[r] = edge_bits<ND, TX, TY, TZ>(x, y, z) & open;
+                G[r] = g.node_base + (min(z0 + z, g.nz - 1) * g.ny + min(y0 + y, g.ny - 1)) * g.nx + min(x0 + x, g.nx - 1);
+                gv[r] = a.g[G[r]];
+                u[r] = a.up[e + nn];
+                ph[r] = T(0);
+                if (E[r]) ph[r] = a.phi[G[r]];
+#pragma unroll
+                for (int d = 0; d < 2 * ND; ++d) c[r][d] = a.pull[e * (2 * ND) + d * S::NT + nn];
             }
 #pragma unroll
             for (int j = 0; j < NIT; ++j) {
                 const int q = threadIdx.x + j * kBlock;
-                if (q >= S::NL) continue;
-                slam[q] = in[j] ? vl[j] : T(0);
-                sup[q] = in[j] ? vu[j] : static_cast<uint8_t>(0);
-                scoef[3 * q + 0] = in[j] ? c0[j] : T(0);
-                scoef[3 * q + 1] = in[j] ? c1[j] : T(0);
-                scoef[3 * q + 2] = in[j] ? c2[j] : T(0);
-            }
-#pragma unroll
-            for (int r = 0; r < NPT; ++r) {
-                const int nn = threadIdx.x + r * kBlock;
-                if (nn >= S::NT) continue;
-                sg[nn] = okn[r] ? vg[r] : T(0);
-                tl.flag[0][nn] = 0u;
-                tl.flag[1][nn] = 0u;
-                tl.dirty[nn] = 0;
+                if (q < S::NL) slam[q] = in[j] ? vl[j] : T(0);
             }
         }
         __syncthreads();
-        // initial list: every node on a first visit, else the nodes on the faces
-        // whose neighbour tile changed
+        // chunks to recompute: every one with a node in the grid on a first
+        // visit, else those with a node on a face whose neighbour tile changed
         const uint32_t m = s_mask;
-        for (int nn = threadIdx.x; nn < S::NT; nn += kBlock) {
-            int x, y, z, L;
-            node_loc<ND, TX, TY, TZ>(nn, x, y, z, L);
-            const bool ok = x0 + x < g.nx && y0 + y < g.ny && z0 + z < g.nz;
-            const int E = edge_bits<ND, TX, TY, TZ>(x, y, z) & open;
-            if (ok && ((m & kAllFaces) || (E & static_cast<int>(m))))
-                tl.list[0][atomicAdd(&tl.cnt[0], 1)] = static_cast<uint16_t>(nn);
+        Mask todo = 0;
+#pragma unroll
+        for (int r = 0; r < S::NPT; ++r) {
+            cur[r] = old[r] = slam[L0 + r * RSTEP];
+            if (ballot64(ok[r] && ((m & kAllFaces) || (E[r] & static_cast<int>(m)))))
+                todo |= Mask(1) << (r * WAVES + wave);
         }
-        __syncthreads();
         bool pending = false;
-        int fm = 0;
-        uint32_t kmin = kNoKey;
         int it = 0;
         for (;; ++it) {
-            const int ncur = tl.cnt[it % 3];
-            if (ncur == 0) break;
+            Mask act[WAVES] = {};
+            if (it > 0) {
+#pragma unroll
+                for (int w = 0; w < WAVES; ++w) act[w] = s_act[((it - 1) & 1) * WAVES + w];
+            }
+            T l[S::NPT][2 * ND];
+#pragma unroll
+            for (int r = 0; r < S::NPT; ++r) {
+                load_nb<T, ND, TX, TY, TZ>(slam, L0 + r * RSTEP, l[r]);
+#pragma unroll
+                for (int d = 0; d < 2 * ND; ++d) asm volatile("" : "+v"(l[r][d]));
+            }
+            if (it > 0) {
+                Mask ch = 0;
+#pragma unroll
+                for (int w = 0; w < WAVES; ++w) ch |= act[w];
+                ch = first_lane(ch);
+                if (ch == 0) break;
+                todo = chunk_reach<ND, TX, TY>(ch);
+            }
             if (it == inner) {
                 pending = true;
                 break;
             }
-            const int cb = it & 1, nb = cb ^ 1;
-            int* ncnt = &tl.cnt[(it + 1) % 3];
-            if (threadIdx.x == 0) tl.cnt[(it + 2) % 3] = 0;
-            for (int i = threadIdx.x; i < ncur; i += kBlock) {
-                const int q = tl.list[cb][i];
-                tl.flag[cb][q] = 0u;
-                int x, y, z, Lq;
-                node_loc<ND, TX, TY, TZ>(q, x, y, z, Lq);
-                // neighbour on the - side of axis k pulls into q if its upwind on
-                // axis k is its + side; on the + side, if its upwind is its - side.
-                // Every neighbour's stencil byte, coefficient and value is read
-                // in one round (all inside the halo block), then summed in
-                // direction order.
-                const int offs[6] = {-1, 1, -SY, SY, -SZ, SZ};
-                uint32_t un[2 * ND];
-                T cn[2 * ND], ln[2 * ND];
+            Mask changed = 0;
 #pragma unroll
-                for (int d = 0; d < 2 * ND; ++d) {
-                    const int p = Lq + offs[d];
-                    un[d] = sup[p];
-                    cn[d] = scoef[3 * p + (d >> 1)];
-                    ln[d] = slam[p];
-                }
-                const T cur = slam[Lq];  // only this lane writes it in this iteration
-                T v = sg[q];
+            for (int r = 0; r < S::NPT; ++r) {
+                const Mask bit = Mask(1) << (r * WAVES + wave);
+                if (!(todo & bit)) continue;
+                // in direction order; a direction that is not pulled adds 0
+                T v = gv[r];
 #pragma unroll
-                for (int d = 0; d < 2 * ND; ++d) {
-                    const int kx = d >> 1;
-                    const uint32_t u = un[d];
-                    const bool present = (u & (1u << (2 * kx))) && !(u & kSrc);
-                    const bool plus = (u >> (2 * kx + 1)) & 1u;
-                    if (present && plus == ((d & 1) == 0)) v = v + cn[d] * ln[d];
-                }
-                if (v != cur) {
-                    slam[Lq] = v;
-                    tl.dirty[q] = 1;
-                    // the nodes upwind of q pull from it: list them
-                    const uint32_t u = sup[Lq];
-                    const int edge = edge_bits<ND, TX, TY, TZ>(x, y, z);
-#pragma unroll
-                    for (int kx = 0; kx < ND; ++kx) {
-                        if (!(u & (1u << (2 * kx))) || (u & kSrc)) continue;
-                        const int d = 2 * kx + static_cast<int>((u >> (2 * kx + 1)) & 1u);  // face toward it
-                        if (edge & (1 << d)) {
-                            if (open & (1 << d)) {
-                                fm |= 1 << d;
-                                const int G = g.node_base + ((z0 + z) * g.ny + (y0 + y)) * g.nx + (x0 + x);
-                                kmin = min(kmin, order_key(-a.phi[G]));
-                            }
-                        } else {
-                            list_add(tl, nb, ncnt, q + node_step<TX, TY>(d));
-                        }
-                    }
-                }
+                for (int d = 0; d < 2 * ND; ++d) v = v + c[r][d] * (c[r][d] != T(0) ? l[r][d] : T(0));
+                const bool diff = ok[r] && v != cur[r];
+                cur[r] = diff ? v : cur[r];
+                slam[L0 + r * RSTEP] = cur[r];  // (only this lane writes it)
+                if (ballot64(diff)) changed |= bit;
             }
+            if (lane0) s_act[(it & 1) * WAVES + wave] = changed;
             __syncthreads();
+        }
+        // write back what changed; across an open face it reaches the node's
+        // upwind neighbour
+        int fm = 0;
+        uint32_t kmin = kNoKey;
+#pragma unroll
+        for (int r = 0; r < S::NPT; ++r) {
+            if (!(cur[r] != old[r])) continue;
+            a.lam[G[r]] = cur[r];
+            const int f = static_cast<int>(u[r]) & E[r];
+            if (f) {
+                fm |= f;
+                kmin = min(kmin, order_key(-ph[r]));
+            }
         }
         if (fm) atomicOr(&s_face, fm);
         if (a.ordered && kmin != kNoKey) atomicMin(&s_kmin, kmin);
@@ -394,12 +419,6 @@ __global__ __launch_bounds__(kBlock, (adj_blocks_per_cu<ND, Shape<ND, TX, TY, TZ
                 push_keyed(a, tn, ntag, key);
             }
         }
-        for (int nn = threadIdx.x; nn < S::NT; nn += kBlock) {
-            if (!tl.dirty[nn]) continue;
-            int x, y, z, L;
-            node_loc<ND, TX, TY, TZ>(nn, x, y, z, L);
-            a.lam[g.node_base + ((z0 + z) * g.ny + (y0 + y)) * g.nx + (x0 + x)] = slam[L];
-        }
         __syncthreads();
     }
     if (threadIdx.x == 0 && visits) stat_add(a.blkstat, SF_VISITS3, visits);
@@ -409,7 +428,7 @@ struct AdjWs {
     Ctl* ctl;
     unsigned long long* blkstat;
     uint8_t* up;
-    void* coef;
+    void* pull;
     void* D;
     void* lam;
     SchedWs q;
@@ -431,8 +450,9 @@ AdjWs adj_layout(char* base, const Batch& b, size_t esz) {
     const size_t n = static_cast<size_t>(b.n);
     w.ctl = reinterpret_cast<Ctl*>(take(sizeof(Ctl)));
     w.blkstat = reinterpret_cast<unsigned long long*>(take(8 * static_cast<size_t>(kStatFields) * kMaxStatBlocks));
-    w.up = reinterpret_cast<uint8_t*>(take(n));
-    w.coef = take(3 * esz * n);
+    const size_t entries = static_cast<size_t>(b.ntiles) * b.cfg.tx * b.cfg.ty * b.cfg.tz;  // tile-major
+    w.up = reinterpret_cast<uint8_t*>(take(entries));
+    w.pull = take(2 * static_cast<size_t>(b.nd) * esz * entries);
     w.D = take(esz * n);
     w.lam = take(esz * n);
     w.q = sched_layout(take, b.ntiles);
@@ -465,23 +485,6 @@ eik_status adj_run(const Batch& b, const T* F, const T* phi, const T* g, T* out,
     HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return launch_ctl_init(w.ctl, s); }));
     HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return launch_zero_words(w.blkstat, blk_bytes, s); }));
     HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return sched_clear(w.q, s); }));
-    HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] {
-        hipLaunchKernelGGL((k_adj_prep<T, ND, TX, TY, TZ>), dim3(tiles), dim3(kBlock), 0, s, G, F, phi, w.up,
-                           static_cast<T*>(w.coef), static_cast<T*>(w.D), static_cast<T*>(w.lam), g);
-        return hipGetLastError();
-    }));
-    launched += 7;
-    for (size_t q = 0; q < b.src.size(); q += kMaxSrcBatch) {
-        SrcBatch<T> sb{};
-        sb.count = static_cast<int>(std::min<size_t>(kMaxSrcBatch, b.src.size() - q));
-        for (int j = 0; j < sb.count; ++j) sb.idx[j] = b.src[q + j].first;
-        HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] {
-            hipLaunchKernelGGL(k_adj_mark_sources<T>, dim3(1), dim3(kMaxSrcBatch), 0, s, sb, w.up,
-                               static_cast<T*>(w.coef), static_cast<T*>(w.D));
-            return hipGetLastError();
-        }));
-        ++launched;
-    }
     // launch t drains list t and fills list t + 1; the seeding fills list 0
     // with tag 1 and the tag chain starts at tag[0] = 1 (claims 2, 3, ...)
     auto iter_args = [&](int64_t t) {
@@ -491,7 +494,7 @@ eik_status adj_run(const Batch& b, const T* F, const T* phi, const T* g, T* out,
         a.g = g;
         a.lam = static_cast<T*>(w.lam);
         a.up = w.up;
-        a.coef = static_cast<const T*>(w.coef);
+        a.pull = static_cast<const T*>(w.pull);
         return a;
     };
     {
@@ -501,8 +504,22 @@ eik_status adj_run(const Batch& b, const T* F, const T* phi, const T* g, T* out,
         a0.key_next = w.q.keys;
         a0.hist_next = w.q.hist_of(0);
         HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] {
-            hipLaunchKernelGGL((k_adj_seed<T, ND, TX, TY, TZ>), dim3(std::min<int64_t>(b.ntiles, 4096)), dim3(kBlock), 0,
-                               s, a0, G);
+            hipLaunchKernelGGL((k_adj_prep<T, ND, TX, TY, TZ>), dim3(tiles), dim3(kBlock), 0, s, a0, G, F, w.up,
+                               static_cast<T*>(w.pull), static_cast<T*>(w.D));
+            return hipGetLastError();
+        }));
+        launched += 6;
+    }
+    for (size_t q = 0; q < b.src.size(); q += kMaxSrcBatch) {
+        SrcBatch<T> sb{};
+        sb.count = static_cast<int>(std::min<size_t>(kMaxSrcBatch, b.src.size() - q));
+        for (int j = 0; j < sb.count; ++j) {
+            sb.idx[j] = b.src[q + j].first;
+            sb.inst[j] = b.src_inst[q + j];
+        }
+        HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] {
+            hipLaunchKernelGGL((k_adj_mark_sources<T, ND, TX, TY, TZ>), dim3(1), dim3(kMaxSrcBatch), 0, s, G, sb, w.up,
+                               static_cast<T*>(w.pull), static_cast<T*>(w.D));
             return hipGetLastError();
         }));
         ++launched;

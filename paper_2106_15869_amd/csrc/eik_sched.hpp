@@ -7,6 +7,8 @@
 
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "eik_device.hpp"
 #include "eik_internal.hpp"
 
@@ -109,6 +111,13 @@ __device__ __forceinline__ int lds_offset(int d) {
         case 4: return -S::SZ;
         default: return S::SZ;
     }
+}
+
+// The neighbour values of LDS node L in direction order (-x, +x, -y, +y, -z, +z).
+template <typename T, int ND, int TX, int TY, int TZ>
+__device__ __forceinline__ void load_nb(const T* lds, int L, T (&nb)[2 * ND]) {
+#pragma unroll
+    for (int d = 0; d < 2 * ND; ++d) nb[d] = lds[L + lds_offset<ND, TX, TY, TZ>(d)];
 }
 
 template <typename T>
@@ -364,7 +373,6 @@ template <int NT>
 struct TileLists {
     uint32_t flag[2][NT];
     uint16_t list[2][NT];
-    uint8_t dirty[NT];  // remedy: node value changed during this visit
     int cnt[3];
 };
 
@@ -374,6 +382,36 @@ __device__ __forceinline__ bool list_add(TileLists<NT>& tl, int nb, int* ncnt, i
     if (atomicExch(&tl.flag[nb][q], 1u) != 0u) return false;
     tl.list[nb][atomicAdd(ncnt, 1)] = static_cast<uint16_t>(q);
     return true;
+}
+
+// ---------------------------------------------------------------------------
+// Dense rounds of a tile visit: chunks of 64 consecutive nodes, one wave each
+// ---------------------------------------------------------------------------
+// A set of a tile's chunks, a bit each.
+template <int NT>
+using ChunkMask = std::conditional_t<(NT <= 32 * 64), uint32_t, unsigned long long>;
+
+// The lanes for which p holds, as a wave-uniform mask.
+__device__ __forceinline__ unsigned long long ballot64(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+
+__device__ __forceinline__ uint32_t first_lane(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ unsigned long long first_lane(unsigned long long v) {
+    return (static_cast<unsigned long long>(first_lane(static_cast<uint32_t>(v >> 32))) << 32) |
+           first_lane(static_cast<uint32_t>(v));
+}
+
+// The chunks (64 consecutive nodes, one wave's share of a round) that hold a
+// neighbour of a node in the chunks of m, m's own among them.
+template <int ND, int TX, int TY, typename Mask>
+__device__ __forceinline__ Mask chunk_reach(Mask m) {
+    static_assert(64 % TX == 0 || TX % 64 == 0, "a neighbouring row lies in the same or the next chunk");
+    Mask r = m | (m << 1) | (m >> 1);
+    if constexpr (ND == 3) {
+        constexpr int ZS = TX * TY / 64;  // chunks per z slice
+        static_assert(TX * TY % 64 == 0, "z slices are whole chunks");
+        if (ZS > 1) r |= (m << ZS) | (m >> ZS);
+    }
+    return r;
 }
 
 // Ordered remedy: before each remedy launch, one lane per entry of the

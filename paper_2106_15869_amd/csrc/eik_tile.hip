@@ -157,13 +157,6 @@ __device__ __forceinline__ void stage(const Inst<T>& g, int x0, int y0, int z0, 
     }
 }
 
-// The neighbour values of LDS node L in direction order (-x, +x, -y, +y, -z, +z).
-template <typename T, int ND, int TX, int TY, int TZ>
-__device__ __forceinline__ void load_nb(const T* sphi, int L, T (&nb)[2 * ND]) {
-#pragma unroll
-    for (int d = 0; d < 2 * ND; ++d) nb[d] = sphi[L + lds_offset<ND, TX, TY, TZ>(d)];
-}
-
 // G_i from the neighbour values (+inf outside the grid).
 // v is the node's H = h / F (isotropic) or its speed F (AN: per-axis spacing,
 // H_k = spacing_k / F); see cell_value.
@@ -219,29 +212,6 @@ struct RemedyLds {
     int* unreached;    // whether a free node was +inf at the start (the tile's first visit)
     int* written;      // values written back
 };
-
-// The lanes for which p holds, as a wave-uniform mask.
-__device__ __forceinline__ unsigned long long ballot64(bool p) { return __builtin_amdgcn_ballot_w64(p); }
-
-__device__ __forceinline__ uint32_t first_lane(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ unsigned long long first_lane(unsigned long long v) {
-    return (static_cast<unsigned long long>(first_lane(static_cast<uint32_t>(v >> 32))) << 32) |
-           first_lane(static_cast<uint32_t>(v));
-}
-
-// The chunks (64 consecutive nodes, one wave's share of a round) that hold a
-// neighbour of a node in the chunks of m, m's own among them.
-template <int ND, int TX, int TY, typename Mask>
-__device__ __forceinline__ Mask chunk_reach(Mask m) {
-    static_assert(64 % TX == 0 || TX % 64 == 0, "a neighbouring row lies in the same or the next chunk");
-    Mask r = m | (m << 1) | (m >> 1);
-    if constexpr (ND == 3) {
-        constexpr int ZS = TX * TY / 64;  // chunks per z slice
-        static_assert(TX * TY % 64 == 0, "z slices are whole chunks");
-        if (ZS > 1) r |= (m << ZS) | (m >> ZS);
-    }
-    return r;
-}
 
 // The remedy rule on tile t at (x0, y0, z0): every lane owns the NPT nodes
 // threadIdx.x + r * kBlock, with their cell values and current values in
@@ -712,7 +682,7 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
     TileIter<T> a, BatchGeom<T> bg, T eps, int inner) {
     using S = Shape<ND, TX, TY, TZ>;
     __shared__ T sphi[S::NL];
-    using Mask = std::conditional_t<(S::NT <= 32 * 64), uint32_t, unsigned long long>;  // a bit per chunk
+    using Mask = ChunkMask<S::NT>;
     __shared__ Mask s_act[2 * kBlock / 64];
     __shared__ int s_len[kSub];
     __shared__ int s_slot;
