@@ -88,7 +88,7 @@ enum {
        first-in first-out, every queued tile in every launch.  By default each
        launch instead processes the
        queued tiles whose pending values are lowest (about a thousand, chosen
-       by a histogram of per-tile keys) and defers the others, so corrections
+       by a sample of per-tile keys) and defers the others, so corrections
        flow roughly in increasing value and fewer nodes are corrected twice.
        Same rules and fixed point either way. */
     EIK_FLAG_FIFO_REMEDY = 16u,

@@ -242,38 +242,23 @@ __global__ __launch_bounds__(kBlock, (adj_blocks_per_cu<ND, Shape<ND, TX, TY, TZ
     __shared__ int s_face;
     __shared__ uint32_t s_mask, s_key, s_kmin;
     const uint32_t ntag = launch_tag(a);
-    __shared__ int s_wlen[kSub];
-    const FirstEntry pre = first_entry(a, true);
-    const int n = list_open(a, s_len, s_wlen);
+    const int n = list_open(a, s_len);
     if (blockIdx.x == 0 && threadIdx.x == 0 && n > 0) a.ctl->iters3 += 1;
-    const bool direct = list_direct(a, n);  // a short list is drained where it is
-    const bool from_work = a.ordered && !direct;
-    const TList src = from_work ? a.work : a.cur;
     const int k = blockIdx.x & (kSub - 1);
-    const int len = from_work ? s_wlen[k] : s_len[k];
+    const int len = s_len[k];
+    if (static_cast<int>(blockIdx.x) / kSub >= len) return;  // no first entry: none at all
+    const uint32_t thr = threadIdx.x < 64 ? sampled_threshold(a, s_len, n) : 0u;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool lane0 = (threadIdx.x & 63) == 0;
     int nx_, ny_, nz_, L0;
     node_loc<ND, TX, TY, TZ>(threadIdx.x, nx_, ny_, nz_, L0);
     unsigned long long visits = 0;
-    for (bool first = true;; first = false) {
+    for (;;) {
         if (threadIdx.x == 0) {
-            const int e = fetch_index(src, k, len, first);
-            const size_t idx = static_cast<size_t>(k) * src.cap + e;
-            const int tt = e < len ? (first ? (from_work ? pre.work : pre.cur) : src.data[idx]) : -1;
+            const int tt = next_tile(a, k, len, visits == 0, thr, ntag, s_key);
             if (tt >= 0) {
-                if (from_work) {
-                    // the split moved the key and dirty faces into the work entry
-                    s_key = first ? pre.key : src.key[idx];
-                    s_mask = first ? pre.mask : src.mask[idx];
-                } else {
-                    if (direct) {
-                        s_key = a.key_cur[tt];
-                        a.key_cur[tt] = kNoKey;
-                    }
-                    s_mask = a.mask_cur[tt];
-                    a.mask_cur[tt] = 0u;
-                }
+                s_mask = a.mask_cur[tt];
+                a.mask_cur[tt] = 0u;
             }
             s_kmin = kNoKey;
             s_face = 0;
@@ -474,7 +459,6 @@ eik_status adj_run(const Batch& b, const T* F, const T* phi, const T* g, T* out,
     const int inner = o.inner_iters > 0 ? o.inner_iters : 4 * (TX + TY + TZ);
     const int dense = static_cast<int>(std::min<int64_t>((b.n + kBlock - 1) / kBlock, 1 << 20));
     const int tiles = static_cast<int>(std::min<int64_t>(b.ntiles, 1 << 16));
-    const int split_blocks = split_blocks_of(b.ntiles);
     const size_t blk_bytes = 8 * static_cast<size_t>(kStatFields) * kMaxStatBlocks;
     int64_t launched = 0;
     Profiler prof;
@@ -502,7 +486,6 @@ eik_status adj_run(const Batch& b, const T* F, const T* phi, const T* g, T* out,
         a0.next = w.q.list_of(0);
         a0.mask_next = w.q.tmask;  // read by launch 0
         a0.key_next = w.q.keys;
-        a0.hist_next = w.q.hist_of(0);
         HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] {
             hipLaunchKernelGGL((k_adj_prep<T, ND, TX, TY, TZ>), dim3(tiles), dim3(kBlock), 0, s, a0, G, F, w.up,
                                static_cast<T*>(w.pull), static_cast<T*>(w.D));
@@ -526,15 +509,8 @@ eik_status adj_run(const Batch& b, const T* F, const T* phi, const T* g, T* out,
     }
     auto step = [&](int64_t t) {
         const AdjIter<T> a = iter_args(t);
-        if (ordered) {
-            const hipError_t e = timed(prof, EIK_KERNEL_OTHER, [&] {
-                hipLaunchKernelGGL(k_tile_split, dim3(split_blocks), dim3(kBlock), 0, s, static_cast<const Sched&>(a));
-                return hipGetLastError();
-            });
-            if (e != hipSuccess) return e;
-        }
         return timed(prof, EIK_KERNEL_ADJOINT, [&] {
-            hipLaunchKernelGGL((k_adj_tile<T, ND, TX, TY, TZ>), dim3(workgroups_of(ND, o.workgroups)), dim3(kBlock), 0,
+            hipLaunchKernelGGL((k_adj_tile<T, ND, TX, TY, TZ>), dim3(workgroups_of(ND, o.workgroups, b.ntiles)), dim3(kBlock), 0,
                                s, a, G, inner);
             return hipGetLastError();
         });
@@ -542,7 +518,7 @@ eik_status adj_run(const Batch& b, const T* F, const T* phi, const T* g, T* out,
     int64_t nl = 0;
     eik_status rc = run_loop(step, [&](int64_t t) { return w.q.count_of(static_cast<int>(t % 3)); }, kSub * kPad, cap,
                              async, s, &nl, w.ctl);
-    launched += (ordered ? 2 : 1) * nl;
+    launched += nl;
     HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] {
         hipLaunchKernelGGL(k_adj_final<T>, dim3(dense), dim3(kBlock), 0, s, static_cast<int>(b.n),
                            static_cast<const T*>(w.D), static_cast<const T*>(w.lam), out);

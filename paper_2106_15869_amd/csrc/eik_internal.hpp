@@ -47,16 +47,28 @@ constexpr int kMaxStatBlocks = 2048;
 constexpr int kWorkgroupStep = 8;
 inline int default_workgroups(int nd) { return nd == 3 ? 1536 : 2048; }
 // The persistent workgroups a call uses (eik_options.workgroups, 0: default).
-inline int workgroups_of(int nd, int32_t opt) { return opt > 0 ? opt : default_workgroups(nd); }
+// No more than the longest list has entries, each sub-list rounded up: an empty
+// launch takes 4.5 us with 2048 of them.
+inline int workgroups_of(int nd, int32_t opt, int64_t ntiles) {
+    const int64_t most = (ntiles + kWorkgroupStep - 1) / kWorkgroupStep * kWorkgroupStep;
+    const int w = opt > 0 ? opt : default_workgroups(nd);
+    return most < w ? static_cast<int>(most) : w;
+}
 
-// Ordered remedy: a launch takes at least this many of the queued tiles with
-// the lowest order keys.  In 3D 1024; a 2D front is a curve and keeps fewer
-// tiles final at a time, 512 (measured: maze 256^3 best at 1024, layered
-// 192^3 5 % faster at 512, 2D lognormal 4096^2 and the paper's Example 5 at
-// 4000^2 3-4 % faster at 512 than at 1024; eik_tune times both).
+// Ordered scheduling: a launch takes at least this many of the queued tiles with
+// the lowest order keys.  A 2D front is a curve and keeps fewer tiles final at a
+// time than a 3D one.
 inline int order_min(int nd) { return nd == 2 ? 512 : 1024; }
 // The per-launch minimum a call uses (eik_options.order_min, 0: default).
 inline int order_min_of(int nd, int32_t opt) { return opt > 0 ? opt : order_min(nd); }
+// The threshold comes from a sample (sampled_threshold in eik_sched.hpp): a
+// launch aims at a quarter more, so that it rarely takes fewer.  Measured
+// against the number aimed at, forward: 2D lognormal 4096^2 11.2 ms at 512, 11.5
+// at 768, 12.1 at 1024, 3000^2 with six sources 3.9, 3.6, 3.6; 3D maze 256^3
+// 4.75 ms at 1024, 4.5 at 1536, 4.55 at 2048, layered 3.0, 2.7, 2.7, lognormal
+// 5.0, 4.8, 5.3.  Adjoint: 2D 1-2 % faster at 768 than at 512; layered 192^3 2.3
+// ms at 1024, 2.5 at 1536.
+inline int order_aim(int omin) { return omin <= (1 << 30) ? omin + omin / 4 : omin; }
 
 // Internal option bit, added after the caller's options are checked (callers
 // cannot set it): a synchronous call reads its list lengths and results back

@@ -29,8 +29,8 @@
 //     listed (first visit) or with the nodes on the faces whose neighbour tile
 //     changed; a drop on a tile face marks that face dirty in the tile across
 //     it and schedules it with the dropped value as its order key.  By
-//     default (ordered remedy) k_tile_split hands each launch only the
-//     lowest-key tiles of the list.
+//     default (ordered remedy) a launch visits only the lowest-key tiles of
+//     its list and sends the others on to the next.
 // Values are updated in place within an inner iteration (a read racing with
 // an update sees either value, both upper bounds of the solution); tiles of
 // one launch see each other's values only through the halo staged at the
@@ -230,13 +230,13 @@ struct RemedyLds {
 // the chain shortened (godunov_mid, neighbours and masks read in one LDS
 // round, a mask word per wave instead of an atomic); maze 256^3 9.07, 6.27,
 // 5.03 ms.
-// The dirty faces are *s.mask, or lane 0's mask_in when set_mask.  Writes the
+// The dirty faces are lane 0's mask_in.  Writes the
 // changed values back and leaves the crossed faces, counts and (ordered) the
 // crossing key in LDS.  Returns the iterations run.
 template <typename T, int ND, int TX, int TY, int TZ, bool AN, typename Mask>
 __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T>& g, int t, int x0, int y0,
                                             int z0, int open, T eps, int inner, bool ordered, uint32_t mask_in,
-                                            bool set_mask, const RemedyLds<T, Mask>& s, bool& pending) {
+                                            const RemedyLds<T, Mask>& s, bool& pending) {
     using S = Shape<ND, TX, TY, TZ>;
     constexpr int WAVES = kBlock / 64;
     static_assert(S::NT % kBlock == 0 && S::NT / 64 <= 8 * sizeof(Mask), "whole rounds, a chunk per bit");
@@ -254,7 +254,7 @@ __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T
         *s.evals = 0;
         *s.written = 0;
         *s.unreached = 0;
-        if (set_mask) *s.mask = mask_in;
+        *s.mask = mask_in;
     }
     __syncthreads();
     const uint32_t m = *s.mask;
@@ -693,33 +693,15 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
     __shared__ uint32_t s_key, s_kmin;
     __shared__ int s_unreached;
     const uint32_t ntag = launch_tag(a);
-    // ordered mode: k_tile_split has moved this launch's tiles into the work
-    // list (the rest went on to the next list)
-    __shared__ int s_wlen[kSub];
-    const int n = list_open(a, s_len, s_wlen);
+    const int n = list_open(a, s_len);
     launch_stats(a, n);
-    const bool direct = list_direct(a, n);  // a short list is drained where it is
-    const bool from_work = a.ordered && !direct;
-    const TList src = from_work ? a.work : a.cur;
     const int k = blockIdx.x & (kSub - 1);
-    const int len = from_work ? s_wlen[k] : s_len[k];
+    const int len = s_len[k];
+    if (static_cast<int>(blockIdx.x) / kSub >= len) return;  // no first entry: none at all
+    const uint32_t thr = threadIdx.x < 64 ? sampled_threshold(a, s_len, n) : 0u;
     unsigned long long evals = 0, early = 0, inner_sum = 0, written = 0, visits = 0;
-    for (bool first = true;; first = false) {
-        if (threadIdx.x == 0) {
-            const int e = fetch_index(src, k, len, first);
-            const size_t idx = static_cast<size_t>(k) * src.cap + e;
-            const int tt = e < len ? src.data[idx] : -1;
-            if (e < len && from_work) {
-                // the split moved the key and dirty faces into the work entry
-                s_key = src.key[idx];
-                s_mask = src.mask[idx];
-            } else if (tt >= 0 && direct) {
-                // the tile leaves the current list: its key goes with it
-                s_key = a.key_cur[tt];
-                a.key_cur[tt] = kNoKey;
-            }
-            s_slot = tt;
-        }
+    for (;;) {
+        if (threadIdx.x == 0) s_slot = next_tile(a, k, len, visits == 0, thr, ntag, s_key);
         __syncthreads();
         const int t = s_slot;
         __syncthreads();
@@ -732,17 +714,15 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
         const int open = open_bits<ND, TX, TY, TZ>(g, x0, y0, z0);
         uint32_t mask_in = 0;
         if (threadIdx.x == 0) {
-            if (!from_work) {
-                // written by the previous launch; no writer during this one
-                mask_in = a.mask_cur[t];
-                a.mask_cur[t] = 0u;
-            }
+            // written by the previous launch; no writer during this one
+            mask_in = a.mask_cur[t];
+            a.mask_cur[t] = 0u;
             s_kmin = kNoKey;
         }
         const RemedyLds<T, Mask> rl{sphi, s_act, &s_mask, &s_face, &s_evals, &s_kmin, &s_unreached, &s_written};
         bool pending;
         const int it = remedy_visit<T, ND, TX, TY, TZ, AN>(a.cells, a.phi, g, t, x0, y0, z0, open, eps, inner,
-                                                           a.ordered, mask_in, !from_work, rl, pending);
+                                                           a.ordered, mask_in, rl, pending);
         // scheduling, one lane per target tile (see the update kernel); the
         // targets are read by the next launch
         if (threadIdx.x < 7) {
@@ -830,7 +810,7 @@ __global__ void k_seed_tiles(Sched a, BatchGeom<T> bg, int nd, int tx_, int ty_,
 __global__ void k_seed_all_tiles(int ntiles, uint32_t* tstamp, TList out) {
     for (int t = blockIdx.x * kBlock + threadIdx.x; t < ntiles; t += gridDim.x * kBlock) {
         tstamp[t] = 1u;
-        out.data[static_cast<size_t>(t & (kSub - 1)) * out.cap + (t / kSub)] = t;
+        out.data[static_cast<size_t>(t & (kSub - 1)) * out.cap + (t / kSub)] = list_entry(t, 0u);
     }
     if (blockIdx.x == 0 && threadIdx.x < kSub)
         out.count[threadIdx.x * kPad] = (ntiles - static_cast<int>(threadIdx.x) + kSub - 1) / kSub;
@@ -844,7 +824,7 @@ struct TileWs {
     unsigned long long* blkstat;
     uint8_t* lab;
     void* cells;        // tile-major cell values (ntiles x tile nodes)
-    SchedWs q;          // lists, stamps, masks, keys, histograms, work lists
+    SchedWs q;          // lists, stamps, masks, keys
     void* table;        // instance table (batches of more than one instance)
     int* tile_inst;     // instance of every tile (idem)
     void* table_u;      // the same for the update step's tiling (2D, see solve_tile)
@@ -1038,7 +1018,7 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
     const int side_u = std::max(cu.tx, std::max(cu.ty, cu.tz));
     const int inner_upd = o.inner_iters > 0 ? o.inner_iters : (b.nd == 2 ? side_u : inner);
     const int ntiles_u = static_cast<int>(B2.ntiles);
-    const int gt = workgroups_of(b.nd, o.workgroups);
+    const int gt = workgroups_of(b.nd, o.workgroups, b.ntiles);
     const int omin = order_min_of(b.nd, o.order_min);
     int64_t launched = 0;
 
@@ -1096,7 +1076,6 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
         a.next = w.q.list_of(t);
         a.mask_next = w.q.tmask + static_cast<size_t>(t & 1) * w.q.ntiles;
         a.key_next = w.q.keys + static_cast<size_t>(t & 1) * w.q.ntiles;
-        a.hist_next = w.q.hist_of(static_cast<int>(t % 3));
         a.ordered = ordered ? 1 : 0;
         a.first = 0;
         return a;
@@ -1104,17 +1083,9 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
     auto detect = [&](int64_t t) {
         return timed(prof, EIK_KERNEL_DETECT, [&] { return k.detect(producer_args(t, 1), geom, eT, gt, s); });
     };
-    const int split_blocks = split_blocks_of(b.ntiles);
     auto visits = [&](int64_t t, int phase, bool first) {
         TileIter<T> a = iter_args(t, phase);
         a.first = first ? 1 : 0;
-        if (ordered) {
-            const hipError_t e = timed(prof, EIK_KERNEL_OTHER, [&] {
-                hipLaunchKernelGGL(k_tile_split, dim3(split_blocks), dim3(kBlock), 0, s, static_cast<const Sched&>(a));
-                return hipGetLastError();
-            });
-            if (e != hipSuccess) return e;
-        }
         // The correcting update step takes every drop: with the tolerance a node
         // may keep a value up to eps above its solve (64^2 float64 at eps =
         // 1e-12: 1.3e-15 from the solution instead of 1e-17).
@@ -1169,7 +1140,7 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
                          [&] { return ku.update(iter_args(t, 0), geom_u, eT, inner_upd, gt, s); });
         },
         counts, kSub * kPad, cap, async, s, &n2, w.ctl, pageable, alone);
-    launched += (ordered && !alone ? 2 : 1) * n2;
+    launched += n2;
     if (rc == EIK_OK && !skip_remedy) {
         // STEP 3: detection adds to the list the next launch drains (what an
         // asynchronous update step left over is still in it), then the remedy
@@ -1189,7 +1160,7 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
                     return visits(n2 + t, 1, t == 0);
                 },
                 [&](int64_t t) { return counts(n2 + t); }, kSub * kPad, cap, async, s, &n3, w.ctl, pageable);
-            launched += (ordered ? 2 : 1) * n3;
+            launched += n3;
         }
     }
     if (async) return rc;

@@ -204,7 +204,7 @@ EIK_API eik_status eik_tune(const void* F, int32_t ndim, const int64_t* dims, do
     }
     const Choice launch = pick;
     for (int v : {1024, 1536, 2048}) {
-        if (v == workgroups_of(ndim, 0)) continue;  // timed already
+        if (v == default_workgroups(ndim)) continue;  // timed already
         Choice c = launch;
         c.workgroups = v;
         const eik_status rc = trial(c);
