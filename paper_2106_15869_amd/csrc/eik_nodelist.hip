@@ -552,15 +552,56 @@ __global__ __launch_bounds__(kBlock) void k_fim_check(NodeIter<T> a, GridDims gd
     app.publish(a.next);
 }
 
+// One dense pass: a lane owns an index of a plane (a row in 2D) and walks
+// `steps` planes along the outer axis, keeping the values behind and ahead in
+// registers, so that a node costs one new value and one speed from memory (the
+// neighbours in the plane are L1 hits) and no division of its index.  Any
+// extents keep all lanes busy but those past the end of the last block.
+// 200 x 333 x 250 float, a whole call: 82 us, 123 us with an index decoded and
+// seven values loaded per node and the general solve (200 MB: 40 us at 5 TB/s).
 template <typename T, int ND>
 __global__ __launch_bounds__(kBlock) void k_apply_local(GridDims gd, const T* __restrict__ F,
                                                         const T* __restrict__ phi, Spacing<T> sp,
-                                                        T* __restrict__ out) {
-    const Grid g = make_grid(gd);
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < g.n; i += gridDim.x * kBlock) {
-        int x, y, z;
-        decode<ND>(g, i, x, y, z);
-        out[i] = eval_node<T, ND>(phi, F, g, i, x, y, z, sp);
+                                                        T* __restrict__ out, int steps) {
+    const T inf = pos_inf<T>();
+    const int plane = ND == 3 ? gd.nx * gd.ny : gd.nx, outer = ND == 3 ? gd.nz : gd.ny;
+    const int p = blockIdx.x * kBlock + threadIdx.x;
+    if (p >= plane) return;
+    const int x = ND == 3 ? p % gd.nx : p;
+    const int y = ND == 3 ? p / gd.nx : 0;
+    const bool x0 = x > 0, x1 = x + 1 < gd.nx, y0 = y > 0, y1 = ND == 3 && y + 1 < gd.ny;
+    for (int o0 = blockIdx.y * steps; o0 < outer; o0 += gridDim.y * steps) {
+        const int end = min(o0 + steps, outer);
+        int i = o0 * plane + p;
+        T behind = o0 > 0 ? phi[i - plane] : inf;
+        T here = phi[i];
+        for (int o = o0; o < end; ++o, i += plane) {
+            const T ahead = o + 1 < outer ? phi[i + plane] : inf;
+            const T f = F[i];
+            T ax = x0 ? phi[i - 1] : inf;
+            if (x1) ax = tmin(ax, phi[i + 1]);
+            T ay = inf;
+            if (ND == 3) {
+                if (y0) ay = phi[i - gd.nx];
+                if (y1) ay = tmin(ay, phi[i + gd.nx]);
+            }
+            const T ao = tmin(behind, ahead);
+            T v;
+            if (sp.aniso) {
+                v = ND == 2 ? local_solve<T, 2>(ao, ax, inf, f, sp) : local_solve<T, 3>(ao, ay, ax, f, sp);
+            } else {
+                const T H = cell_H(sp.h, f);
+                if (__builtin_amdgcn_ballot_w64(H < inf && !mid_range(H)) == 0) {
+                    v = ND == 2 ? godunov_mid<T, 2>(ao, ax, inf, H, H * H) : godunov_mid<T, 3>(ao, ay, ax, H, H * H);
+                    if (!(H < inf) || !(tmin(tmin(ao, ax), ay) < inf)) v = inf;
+                } else {
+                    v = ND == 2 ? godunov<T, 2>(ao, ax, inf, H) : godunov<T, 3>(ao, ay, ax, H);
+                }
+            }
+            out[i] = v;
+            behind = here;
+            here = ahead;
+        }
     }
 }
 
@@ -717,12 +758,16 @@ hipError_t launch_remedy(const GridDims& g, const NodeIter<T>& it, const Spacing
 template <typename T>
 hipError_t launch_apply_local(const GridDims& g, const T* F, const T* phi, const Spacing<T>& h, T* out,
                               hipStream_t s) {
+    const int plane = g.nd == 3 ? g.nx * g.ny : g.nx, outer = g.nd == 3 ? g.nz : g.ny;
+    // Planes per walk: the two values at its ends are read by the next walk
+    // too, so long walks, but at least half a million lanes (four waves for
+    // each of the 1024 SIMDs twice over).
+    const int steps = std::max(1, std::min(16, g.n >> 19));
+    const dim3 grid((plane + kBlock - 1) / kBlock, std::min((outer + steps - 1) / steps, 65535));
     if (g.nd == 2)
-        hipLaunchKernelGGL((k_apply_local<T, 2>), dim3(dense_blocks(g.n)), dim3(kBlock), 0, s, g, F,
-                           phi, h, out);
+        hipLaunchKernelGGL((k_apply_local<T, 2>), grid, dim3(kBlock), 0, s, g, F, phi, h, out, steps);
     else
-        hipLaunchKernelGGL((k_apply_local<T, 3>), dim3(dense_blocks(g.n)), dim3(kBlock), 0, s, g, F,
-                           phi, h, out);
+        hipLaunchKernelGGL((k_apply_local<T, 3>), grid, dim3(kBlock), 0, s, g, F, phi, h, out, steps);
     return hipGetLastError();
 }
 
