@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kBlock, (adj_blocks_per_cu<ND, Shape<ND, TX, TY, TZ
     __shared__ uint32_t s_mask, s_key, s_kmin;
     const uint32_t ntag = launch_tag(a);
     const int n = list_open(a, s_len);
-    if (blockIdx.x == 0 && threadIdx.x == 0 && n > 0) a.ctl->iters3 += 1;
+    launch_stats(a, n);
     const int k = blockIdx.x & (kSub - 1);
     const int len = s_len[k];
     if (static_cast<int>(blockIdx.x) / kSub >= len) return;  // no first entry: none at all
@@ -466,14 +466,17 @@ eik_status adj_run(const Batch& b, const T* F, const T* phi, const T* g, T* out,
 
     BatchGeom<T> G;
     HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return upload_batch_geom<T>(b, w.table, w.tile_inst, s, G, launched); }));
-    HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return launch_ctl_init(w.ctl, s); }));
-    HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return launch_zero_words(w.blkstat, blk_bytes, s); }));
-    HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return sched_clear(w.q, s); }));
+    ClearPlan clear;
+    clear.ctl = w.ctl;
+    clear.add(w.blkstat, blk_bytes);
+    sched_clear(w.q, clear);
+    HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return launch_clear(clear, s); }));
     // launch t drains list t and fills list t + 1; the seeding fills list 0
     // with tag 1 and the tag chain starts at tag[0] = 1 (claims 2, 3, ...)
     auto iter_args = [&](int64_t t) {
         AdjIter<T> a{};
         sched_fill(a, w.q, t, ordered, order_min_of(ND, o.order_min), static_cast<int>(t & 1), 1, w.ctl, w.blkstat);
+        if (!async) a.mail = host_slots().mail + (t & (HostSlots::kMail - 1));
         a.phi = phi;
         a.g = g;
         a.lam = static_cast<T*>(w.lam);
@@ -491,7 +494,7 @@ eik_status adj_run(const Batch& b, const T* F, const T* phi, const T* g, T* out,
                                static_cast<T*>(w.pull), static_cast<T*>(w.D));
             return hipGetLastError();
         }));
-        launched += 6;
+        launched += 2;
     }
     for (size_t q = 0; q < b.src.size(); q += kMaxSrcBatch) {
         SrcBatch<T> sb{};
@@ -516,8 +519,9 @@ eik_status adj_run(const Batch& b, const T* F, const T* phi, const T* g, T* out,
         });
     };
     int64_t nl = 0;
-    eik_status rc = run_loop(step, [&](int64_t t) { return w.q.count_of(static_cast<int>(t % 3)); }, kSub * kPad, cap,
-                             async, s, &nl, w.ctl);
+    auto counts = [&](int64_t t) { return w.q.count_of(static_cast<int>(t % 3)); };
+    eik_status rc = async ? run_loop(step, counts, kSub * kPad, cap, true, s, &nl, w.ctl)
+                          : run_tile_loop(step, counts, kSub * kPad, 0, cap, s, &nl);
     launched += nl;
     HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] {
         hipLaunchKernelGGL(k_adj_final<T>, dim3(dense), dim3(kBlock), 0, s, static_cast<int>(b.n),
@@ -526,14 +530,13 @@ eik_status adj_run(const Batch& b, const T* F, const T* phi, const T* g, T* out,
     }));
     ++launched;
     if (async) return rc;
-    HostSlots& hs = host_slots();
-    HIP_TRY(hipMemcpyAsync(hs.ctl, w.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(hs.blk, w.blkstat, blk_bytes, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    Results res;
+    const eik_status rr = read_results(w.ctl, w.blkstat, kMaxStatBlocks, false, s, res);
+    if (rr != EIK_OK) return rr;
     if (st) {
         *st = eik_stats{};
-        st->step3_iters = static_cast<int64_t>(hs.ctl->iters3);
-        st->tile_visits_step3 = static_cast<int64_t>(blk_sum(hs.blk, SF_VISITS3, kMaxStatBlocks));
+        st->step3_iters = static_cast<int64_t>(res.ctl.iters3);
+        st->tile_visits_step3 = static_cast<int64_t>(res.sum[SF_VISITS3]);
         st->launches = launched;
         HIP_TRY(prof.collect(st));
     }

@@ -42,17 +42,18 @@ eik_status solve_entry(const void* F, int32_t ndim, const int64_t* dims, double 
 // Pinned host words for counter read-back (one set per host thread).
 struct HostSlots {
     static constexpr int kWords = 8192;  // two slots of segment lengths
+    static constexpr int kMail = 64;
     int* words = nullptr;
-    Ctl* ctl = nullptr;
-    unsigned long long* blk = nullptr;   // per-workgroup statistics read-back
+    int* mail = nullptr;          // list lengths the kernels report (run_tile_loop)
+    Results* results = nullptr;   // written by launch_results
     hipEvent_t ev[2] = {nullptr, nullptr};
     bool ok = false;
     HostSlots() {
+        // written by kernels: coherent, so that the host sees the stores
+        constexpr unsigned flags = hipHostMallocMapped | hipHostMallocCoherent;
         if (hipHostMalloc(reinterpret_cast<void**>(&words), kWords * sizeof(int)) != hipSuccess) return;
-        if (hipHostMalloc(reinterpret_cast<void**>(&ctl), sizeof(Ctl)) != hipSuccess) return;
-        if (hipHostMalloc(reinterpret_cast<void**>(&blk), sizeof(unsigned long long) * kStatFields *
-                                                              kMaxStatBlocks) != hipSuccess)
-            return;
+        if (hipHostMalloc(reinterpret_cast<void**>(&mail), kMail * sizeof(int), flags) != hipSuccess) return;
+        if (hipHostMalloc(reinterpret_cast<void**>(&results), sizeof(Results), flags) != hipSuccess) return;
         if (hipEventCreateWithFlags(&ev[0], hipEventDisableTiming) != hipSuccess) return;
         if (hipEventCreateWithFlags(&ev[1], hipEventDisableTiming) != hipSuccess) return;
         ok = true;
@@ -133,14 +134,6 @@ inline hipError_t timed(Profiler& p, int kind, Fn fn) {
     e = fn();
     if (e != hipSuccess) return e;
     return p.end();
-}
-
-// Sum the per-workgroup statistics columns (after the stream was synchronised
-// and `blk` copied to hs.blk).
-inline unsigned long long blk_sum(const unsigned long long* blk, int field, int nblocks) {
-    unsigned long long v = 0;
-    for (int b = 0; b < nblocks; ++b) v += blk[field * nblocks + b];
-    return v;
 }
 
 // Run `step(t)` for t = 0, 1, ... until the list a step would consume is
@@ -238,17 +231,61 @@ inline eik_status list_total(const int* counts, int nseg, hipStream_t s, bool pa
     return EIK_OK;
 }
 
-// The control block and the statistics totals of a synchronous call, after
-// its last kernel: through the per-thread pinned slots, or (pageable) by
-// summing the statistics on the device and copying the totals into *r.
-struct Results {
-    Ctl ctl;
-    unsigned long long sum[kStatFields];
-};
+// run_loop for a synchronous call whose launch t reports the length of the list
+// it finds in mail[t % kMail] (pinned): the host reads the word after the
+// chunk's event, so that no copy stands between the launches (4 us and a gap
+// each), and a chunk can be short: about two are enqueued past the end.
+template <typename StepFn, typename CountsFn>
+inline eik_status run_tile_loop(StepFn step, CountsFn counts, int nseg, int64_t first, int64_t max_iters, hipStream_t s,
+                                int64_t* steps) {
+    HostSlots& hs = host_slots();
+    if (!hs.ok) return fail(EIK_ERR_DEVICE, "pinned host buffer allocation failed");
+    const int64_t chunk = 4;
+    auto found = [&](int64_t t) {
+        return *const_cast<volatile int*>(hs.mail + ((first + t) & (HostSlots::kMail - 1)));
+    };
+    int64_t t = 0, before = 0;
+    int slot = 0;
+    for (;;) {
+        const int64_t end = std::min(max_iters, t + chunk);
+        for (; t < end; ++t) HIP_TRY(step(t));
+        HIP_TRY(hipEventRecord(hs.ev[slot], s));
+        if (before > 0) {
+            HIP_TRY(hipEventSynchronize(hs.ev[slot ^ 1]));
+            if (found(before - 1) == 0) break;
+        }
+        if (t >= max_iters) {
+            HIP_TRY(hipEventSynchronize(hs.ev[slot]));
+            bool open = found(t - 1) != 0;
+            if (open) {
+                const eik_status rc = list_total(counts(t), nseg, s, false, open);
+                if (rc != EIK_OK) return rc;
+            }
+            if (!open) break;
+            *steps = t;
+            return fail(EIK_ERR_NO_CONVERGENCE, "iteration cap reached");
+        }
+        before = t;
+        slot ^= 1;
+    }
+    *steps = t;
+    return EIK_OK;
+}
 
+// The control block and the statistics totals of a synchronous call, after its
+// last kernel, and whether the list of `nseg` length words (if any) holds
+// anything: through the per-thread pinned slots, or (pageable) by summing the
+// statistics on the device and copying.
 inline eik_status read_results(const Ctl* dctl, unsigned long long* blkstat, int nblocks, bool pageable,
-                               hipStream_t s, Results& r) {
+                               hipStream_t s, Results& r, const int* counts = nullptr, int nseg = 0) {
     if (pageable) {
+        bool open = false;
+        if (counts) {
+            const eik_status rc = list_total(counts, nseg, s, true, open);
+            if (rc != EIK_OK) return rc;
+        }
+        r.open = open ? 1 : 0;
+        if (open) return EIK_OK;  // the caller goes on and reads the results later
         HIP_TRY(launch_sum_stats(blkstat, nblocks, s));
         HIP_TRY(hipMemcpyAsync(&r.ctl, dctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipMemcpyAsync(r.sum, blkstat, sizeof(r.sum), hipMemcpyDeviceToHost, s));
@@ -257,12 +294,9 @@ inline eik_status read_results(const Ctl* dctl, unsigned long long* blkstat, int
     }
     HostSlots& hs = host_slots();
     if (!hs.ok) return fail(EIK_ERR_DEVICE, "pinned host buffer allocation failed");
-    HIP_TRY(hipMemcpyAsync(hs.ctl, dctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(hs.blk, blkstat, sizeof(unsigned long long) * kStatFields * nblocks,
-                           hipMemcpyDeviceToHost, s));
+    HIP_TRY(launch_results(dctl, blkstat, nblocks, counts, nseg, hs.results, s));
     HIP_TRY(hipStreamSynchronize(s));
-    r.ctl = *hs.ctl;
-    for (int f = 0; f < kStatFields; ++f) r.sum[f] = blk_sum(hs.blk, f, nblocks);
+    r = *hs.results;
     return EIK_OK;
 }
 

@@ -179,7 +179,21 @@ template <typename T>
 hipError_t launch_remedy(const GridDims& g, const NodeIter<T>& it, const Spacing<T>& h, T eps, bool det, hipStream_t s);
 hipError_t launch_seg_clear(int* count, int nseg, hipStream_t s);
 hipError_t launch_zero_words(void* p, size_t bytes, hipStream_t s);
-hipError_t launch_fill_words(void* p, size_t n, uint32_t v, hipStream_t s);  // n 32-bit words
+// Initialise the control block and set regions of 32-bit words, in one launch.
+struct ClearPlan {
+    static constexpr int kMost = 6;
+    Ctl* ctl = nullptr;
+    int count = 0;
+    struct Region {
+        uint32_t* p;
+        size_t words;
+        uint32_t value;
+    } region[kMost];
+    void add(void* p, size_t bytes, uint32_t value = 0u) {
+        region[count++] = Region{static_cast<uint32_t*>(p), bytes / 4, value};
+    }
+};
+hipError_t launch_clear(const ClearPlan& c, hipStream_t s);
 template <typename T>
 hipError_t launch_apply_local(const GridDims& g, const T* F, const T* phi, const Spacing<T>& h, T* out,
                               hipStream_t s);
@@ -191,6 +205,16 @@ hipError_t launch_ctl_init(Ctl* ctl, hipStream_t s);
 // length words of the list the next launch would drain and records in
 // ctl->open_lists whether it is non-empty.
 hipError_t launch_loop_status(Ctl* ctl, const int* counts, int nseg, hipStream_t s);
+// The control block, the statistics totals and whether the list of `nseg`
+// length words holds anything, as a synchronous call reads them back.
+struct Results {
+    Ctl ctl;
+    unsigned long long sum[kStatFields];
+    int open;
+};
+// Writes them to pinned host memory: one kernel in place of two or three copies.
+hipError_t launch_results(const Ctl* ctl, const unsigned long long* blkstat, int nblocks, const int* counts, int nseg,
+                          Results* out, hipStream_t s);
 // Sums each statistics field of a [kStatFields][nblocks] array into its
 // first kStatFields words.
 hipError_t launch_sum_stats(unsigned long long* blkstat, int nblocks, hipStream_t s);

@@ -126,10 +126,6 @@ __global__ void k_zero_words(uint32_t* p, int n) {
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) p[i] = 0u;
 }
 
-__global__ void k_fill_words(uint32_t* p, int n, uint32_t v) {
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) p[i] = v;
-}
-
 // ---------------------------------------------------------------------------
 // STEP 2
 // ---------------------------------------------------------------------------
@@ -610,16 +606,53 @@ __global__ void k_reset_counters(Ctl* ctl) {
 }
 
 // Zero the whole control block (runs before any kernel of a solve).
+__device__ __forceinline__ void ctl_init(Ctl* ctl) {
+    for (int k = 0; k < 4; ++k) ctl->cnt[k] = 0;
+    ctl->err = 0;
+    ctl->open_lists = 0;
+    ctl->tag[0] = 1;
+    ctl->tag[1] = 1;
+    ctl->iters2 = ctl->iters3 = ctl->evals2 = ctl->evals_det = ctl->evals_rem = 0;
+    ctl->remedy_init = ctl->max_active = 0;
+    ctl->visits2 = ctl->visits3 = ctl->inner2 = ctl->inner3 = 0;
+}
 __global__ void k_ctl_init(Ctl* ctl) {
+    if (threadIdx.x == 0) ctl_init(ctl);
+}
+
+__global__ __launch_bounds__(kBlock) void k_clear(ClearPlan c) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctl_init(c.ctl);
+    for (int r = 0; r < c.count; ++r) {
+        const ClearPlan::Region g = c.region[r];
+        for (size_t i = static_cast<size_t>(blockIdx.x) * kBlock + threadIdx.x; i < g.words;
+             i += static_cast<size_t>(gridDim.x) * kBlock)
+            g.p[i] = g.value;
+    }
+}
+
+// Block f sums statistics field f, the last block reads the rest.
+__global__ __launch_bounds__(kBlock) void k_results(const Ctl* ctl, const unsigned long long* blk, int nblocks,
+                                                    const int* counts, int nseg, Results* out) {
+    const int f = blockIdx.x;
+    if (f < kStatFields) {
+        __shared__ unsigned long long part[kBlock];
+        unsigned long long v = 0;
+        for (int b = threadIdx.x; b < nblocks; b += kBlock) v += blk[f * nblocks + b];
+        part[threadIdx.x] = v;
+        __syncthreads();
+        for (int w = kBlock / 2; w > 0; w >>= 1) {
+            if (static_cast<int>(threadIdx.x) < w) part[threadIdx.x] += part[threadIdx.x + w];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) out->sum[f] = part[0];
+        return;
+    }
+    int any = 0;
+    for (int k = threadIdx.x; k < nseg; k += kBlock) any |= counts[k] != 0;
+    any = __syncthreads_or(any);
     if (threadIdx.x == 0) {
-        for (int k = 0; k < 4; ++k) ctl->cnt[k] = 0;
-        ctl->err = 0;
-        ctl->open_lists = 0;
-        ctl->tag[0] = 1;
-        ctl->tag[1] = 1;
-        ctl->iters2 = ctl->iters3 = ctl->evals2 = ctl->evals_det = ctl->evals_rem = 0;
-        ctl->remedy_init = ctl->max_active = 0;
-        ctl->visits2 = ctl->visits3 = ctl->inner2 = ctl->inner3 = 0;
+        out->ctl = *ctl;
+        out->open = any;
     }
 }
 
@@ -695,10 +728,17 @@ hipError_t launch_zero_words(void* p, size_t bytes, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_fill_words(void* p, size_t n, uint32_t v, hipStream_t s) {
-    const int m = static_cast<int>(n);
-    hipLaunchKernelGGL(k_fill_words, dim3(std::min((m + kBlock - 1) / kBlock, 1024)), dim3(kBlock), 0, s,
-                       static_cast<uint32_t*>(p), m, v);
+hipError_t launch_clear(const ClearPlan& c, hipStream_t s) {
+    size_t most = 1;
+    for (int r = 0; r < c.count; ++r) most = std::max(most, c.region[r].words);
+    const int blocks = static_cast<int>(std::min<size_t>((most + kBlock - 1) / kBlock, 1024));
+    hipLaunchKernelGGL(k_clear, dim3(blocks), dim3(kBlock), 0, s, c);
+    return hipGetLastError();
+}
+
+hipError_t launch_results(const Ctl* ctl, const unsigned long long* blkstat, int nblocks, const int* counts, int nseg,
+                          Results* out, hipStream_t s) {
+    hipLaunchKernelGGL(k_results, dim3(kStatFields + 1), dim3(kBlock), 0, s, ctl, blkstat, nblocks, counts, nseg, out);
     return hipGetLastError();
 }
 

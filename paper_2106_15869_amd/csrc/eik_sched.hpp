@@ -66,6 +66,7 @@ struct Sched {
     int* zero_fetch;
     Ctl* ctl;
     unsigned long long* blkstat;  // [kStatFields][kMaxStatBlocks], column blockIdx % kMaxStatBlocks
+    int* mail;  // where the launch reports the length of the list it found (pinned host word; may be NULL)
     int tag_slot;
     int phase;  // 0 update step, 1 remedy (or adjoint) loop
     int first;  // first launch of its loop
@@ -139,6 +140,7 @@ __device__ __forceinline__ void launch_stats(const Sched& a, int n) {
             }
         }
         if (a.first) a.ctl->remedy_init = un;
+        if (a.mail) __hip_atomic_store(a.mail, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -439,11 +441,10 @@ inline void sched_fill(Sched& a, const SchedWs& w, int64_t t, bool ordered, int 
 }
 
 // Before a solve: stamps and masks zero, list counters zero, order keys "none".
-inline hipError_t sched_clear(const SchedWs& w, hipStream_t s) {
-    hipError_t e = launch_zero_words(w.tstamp, 4 * (static_cast<size_t>(w.tmask - w.tstamp) + 2 * static_cast<size_t>(w.ntiles)), s);
-    if (e == hipSuccess) e = launch_zero_words(w.counters, kCounterBytes, s);
-    if (e == hipSuccess) e = launch_fill_words(w.keys, 2 * static_cast<size_t>(w.ntiles), kNoKey, s);
-    return e;
+inline void sched_clear(const SchedWs& w, ClearPlan& c) {
+    c.add(w.tstamp, 4 * (static_cast<size_t>(w.tmask - w.tstamp) + 2 * static_cast<size_t>(w.ntiles)));
+    c.add(w.counters, kCounterBytes);
+    c.add(w.keys, 8 * static_cast<size_t>(w.ntiles), kNoKey);
 }
 
 }  // namespace

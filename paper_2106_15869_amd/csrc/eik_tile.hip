@@ -752,20 +752,21 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
 
 
 // ---------------------------------------------------------------------------
-// Tile-major cell values
+// STEP 1
 // ---------------------------------------------------------------------------
-// Entry t * NT + n holds the cell value of node n of tile t (H = h / F, or F
-// itself with per-axis spacing; +inf / 0 on a barrier), -1 for a fixed node,
-// the dead value outside the grid.  Built once per solve, after seeding: a
-// tile's detection and visits then read one contiguous block
-// instead of a row of F per cache line and a label byte per node, and do not
-// divide.  (NT is a multiple of 64, so a wave's entries share one tile.)
+// Tile-major cell values: entry t * NT + n holds the cell value of node n of
+// tile t (H = h / F, or F itself with per-axis spacing; +inf / 0 on a barrier),
+// -1 for a fixed node (k_tile_sources), the dead value outside the grid.  A
+// tile's detection and visits then read one contiguous block instead of a row
+// of F per cache line and a label byte per node, and do not divide.  In the same
+// pass: every value +inf, and the check of F.
 template <typename T, int ND, int TX, int TY, int TZ, bool AN>
-__global__ __launch_bounds__(kBlock) void k_build_cells(BatchGeom<T> bg, const T* __restrict__ F,
-                                                        const uint8_t* __restrict__ lab, T* __restrict__ cells) {
+__global__ __launch_bounds__(kBlock) void k_tile_init(BatchGeom<T> bg, const T* __restrict__ F, T* __restrict__ phi,
+                                                      T* __restrict__ cells, Ctl* ctl) {
     using S = Shape<ND, TX, TY, TZ>;
     static_assert(S::NT % 64 == 0, "a wave's entries must lie in one tile");
     const int64_t total = static_cast<int64_t>(bg.ntiles) * S::NT;
+    bool bad = false;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < total;
          i += static_cast<int64_t>(gridDim.x) * kBlock) {
         const int t = static_cast<int>(i / S::NT);
@@ -776,25 +777,35 @@ __global__ __launch_bounds__(kBlock) void k_build_cells(BatchGeom<T> bg, const T
         bool ok;
         const int G = owned_index<T, ND, TX, TY, TZ>(g, tx * TX, ty * TY, tz * (ND == 3 ? TZ : 1), n, ok);
         T v = dead_value<T, AN>();
-        if (ok) v = (lab[G] & 3u) == L_FIXED ? fixed_cell<T>() : cell_value<T, AN>(g, F[G]);
+        if (ok) {
+            const T f = F[G];
+            bad |= !(f >= T(0)) || !(f < pos_inf<T>());
+            v = cell_value<T, AN>(g, f);
+            phi[G] = pos_inf<T>();
+        }
         cells[i] = v;
     }
+    if (ballot64(bad) && lane_id() == 0) atomicOr(&ctl->err, 1);
 }
 
-// ---------------------------------------------------------------------------
-// STEP 1 helpers
-// ---------------------------------------------------------------------------
-
-// Initial tile list: tiles holding a grid neighbour of a source (a's next
-// list and tag), every node of them to be evaluated, ordered by the source's
-// value.
+// Sources: values and fixed cells.  With `queue`, the tiles holding a grid
+// neighbour of a source enter a's next list, every node of them to be
+// evaluated, ordered by the source's value.  (cells may be NULL: the update
+// step alone takes sources from the labels.)
 template <typename T>
-__global__ void k_seed_tiles(Sched a, BatchGeom<T> bg, int nd, int tx_, int ty_, int tz_, SrcBatch<T> b) {
+__global__ void k_tile_sources(Sched a, BatchGeom<T> bg, int nd, int tx_, int ty_, int tz_, SrcBatch<T> b, T* phi,
+                               T* cells, int queue) {
     const int k = threadIdx.x;
     if (k >= b.count) return;
     const Inst<T> g = bg.ninst == 1 ? bg.one : bg.table[b.inst[k]];
     const int i = b.idx[k] - g.node_base;
     const int x = i % g.nx, y = (i / g.nx) % g.ny, z = i / (g.nx * g.ny);
+    phi[b.idx[k]] = b.val[k];
+    if (cells) {
+        const size_t t = g.tile_base + ((z / tz_) * g.nty + (y / ty_)) * g.ntx + (x / tx_);
+        cells[t * (tx_ * ty_ * tz_) + ((z % tz_) * ty_ + y % ty_) * tx_ + x % tx_] = fixed_cell<T>();
+    }
+    if (!queue) return;
     const int dx[6] = {-1, 1, 0, 0, 0, 0}, dy[6] = {0, 0, -1, 1, 0, 0}, dz[6] = {0, 0, 0, 0, -1, 1};
     for (int d = 0; d < 2 * nd; ++d) {
         const int X = x + dx[d], Y = y + dy[d], Z = z + dz[d];
@@ -883,11 +894,11 @@ struct TileKernels {
         hipLaunchKernelGGL((k_tile_remedy<T, ND, TX, TY, TZ, AN>), dim3(gt), dim3(kBlock), 0, s, a, g, eps, inner);
         return hipGetLastError();
     }
-    static hipError_t cells(const BatchGeom<T>& g, const T* F, const uint8_t* lab, T* out, hipStream_t s) {
+    static hipError_t init(const BatchGeom<T>& g, const T* F, T* phi, T* cells, Ctl* ctl, hipStream_t s) {
         using S = Shape<ND, TX, TY, TZ>;
         const int64_t total = static_cast<int64_t>(g.ntiles) * S::NT;
         const int blocks = static_cast<int>(std::min<int64_t>((total + kBlock - 1) / kBlock, 8192));
-        hipLaunchKernelGGL((k_build_cells<T, ND, TX, TY, TZ, AN>), dim3(blocks), dim3(kBlock), 0, s, g, F, lab, out);
+        hipLaunchKernelGGL((k_tile_init<T, ND, TX, TY, TZ, AN>), dim3(blocks), dim3(kBlock), 0, s, g, F, phi, cells, ctl);
         return hipGetLastError();
     }
 };
@@ -897,7 +908,7 @@ struct TileOps {
     hipError_t (*update)(const TileIter<T>&, const BatchGeom<T>&, T, int, int, hipStream_t) = nullptr;
     hipError_t (*detect)(const TileIter<T>&, const BatchGeom<T>&, T, int, hipStream_t) = nullptr;
     hipError_t (*remedy)(const TileIter<T>&, const BatchGeom<T>&, T, int, int, hipStream_t) = nullptr;
-    hipError_t (*cells)(const BatchGeom<T>&, const T*, const uint8_t*, T*, hipStream_t) = nullptr;
+    hipError_t (*init)(const BatchGeom<T>&, const T*, T*, T*, Ctl*, hipStream_t) = nullptr;
 };
 
 template <typename T, int ND, int TX, int TY, int TZ, bool AN = false>
@@ -906,7 +917,7 @@ TileOps<T> ops_of() {
     k.update = &TileKernels<T, ND, TX, TY, TZ, AN>::update;
     k.detect = &TileKernels<T, ND, TX, TY, TZ, AN>::detect;
     k.remedy = &TileKernels<T, ND, TX, TY, TZ, AN>::remedy;
-    k.cells = &TileKernels<T, ND, TX, TY, TZ, AN>::cells;
+    k.init = &TileKernels<T, ND, TX, TY, TZ, AN>::init;
     return k;
 }
 
@@ -1033,11 +1044,24 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
         }));
     else
         geom_u = geom;
-    HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return launch_ctl_init(w.ctl, s); }));
-    HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return launch_zero_words(w.blkstat, blk_bytes, s); }));
-    HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return launch_init<T>(F, phi, w.lab, nullptr, static_cast<int>(b.n), w.ctl, s); }));
-    HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return sched_clear(w.q, s); }));
-    launched += 7;
+    ClearPlan clear;
+    clear.ctl = w.ctl;
+    clear.add(w.blkstat, blk_bytes);
+    sched_clear(w.q, clear);
+    HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return launch_clear(clear, s); }));
+    // +inf everywhere, cell values for the visits and detection; the update step
+    // alone works from labels
+    if (alone) {
+        HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] {
+            return launch_init<T>(F, phi, w.lab, nullptr, static_cast<int>(b.n), w.ctl, s);
+        }));
+        launched += 1;
+    }
+    if (!skip_remedy) {
+        HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return k.init(geom, F, phi, static_cast<T*>(w.cells), w.ctl, s); }));
+        launched += 1;
+    }
+    launched += 1;
     const bool ordered = (o.flags & EIK_FLAG_FIFO_REMEDY) == 0;
     std::vector<SrcBatch<T>> batches;
     for (size_t q = 0; q < b.src.size(); q += kMaxSrcBatch) {
@@ -1050,9 +1074,11 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
         }
         batches.push_back(sb);
     }
-    for (auto& sb : batches)
-        HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return launch_seed<T>(phi, w.lab, sb, s); }));
-    launched += static_cast<int64_t>(batches.size());
+    if (alone) {
+        for (auto& sb : batches)
+            HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return launch_seed<T>(phi, w.lab, sb, s); }));
+        launched += static_cast<int64_t>(batches.size());
+    }
 
     const T eT = static_cast<T>(eps);
     // The launches of a solve form one chain: launch t drains list t and fills
@@ -1062,6 +1088,7 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
         TileIter<T> a{};
         sched_fill(a, w.q, t, ordered && !(alone && phase == 0), omin, static_cast<int>(t & 1), phase, w.ctl,
                    w.blkstat);
+        if (!async && !pageable) a.mail = host_slots().mail + (t & (HostSlots::kMail - 1));
         a.F = F;
         a.phi = phi;
         a.lab = w.lab;
@@ -1094,32 +1121,34 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
     };
     auto counts = [&](int64_t t) { return w.q.count_of(static_cast<int>(t % 3)); };
 
-    // Cell values for the visits and detection (sources are fixed by now).
-    if (!skip_remedy) {
-        HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] { return k.cells(geom, F, w.lab, static_cast<T*>(w.cells), s); }));
-        launched += 1;
-    }
-    // Initial list: the tiles next to the sources; with many sources a dense
-    // pass finds them.  (One launch per 64 sources up to 8 of them, about what
-    // the dense pass over a 4 M node grid costs.)
-    if (batches.size() <= 8) {
-        TileIter<T> a = producer_args(0, 0);
-        if (alone) a.ordered = 0;
+    // Sources, and the initial list: the tiles next to them; with many sources a
+    // dense pass finds those.  (One launch per 64 sources up to 8 of them, about
+    // what the dense pass over a 4 M node grid costs.)
+    const bool queue = batches.size() <= 8;
+    TileIter<T> a0 = producer_args(0, 0);
+    if (alone) a0.ordered = 0;
+    auto sources = [&](const BatchGeom<T>& g, const TileCfg& tc, T* cells, bool q) {
         for (auto& sb : batches)
             HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] {
-                hipLaunchKernelGGL(k_seed_tiles<T>, dim3(1), dim3(kMaxSrcBatch), 0, s, static_cast<const Sched&>(a),
-                                   geom_u, b.nd, cu.tx, cu.ty, cu.tz, sb);
+                hipLaunchKernelGGL(k_tile_sources<T>, dim3(1), dim3(kMaxSrcBatch), 0, s, static_cast<const Sched&>(a0), g,
+                                   b.nd, tc.tx, tc.ty, tc.tz, sb, phi, cells, q ? 1 : 0);
                 return hipGetLastError();
             }));
         launched += static_cast<int64_t>(batches.size());
-    } else if (alone) {
+        return EIK_OK;
+    };
+    // (the update step alone may queue tiles of another shape than the cells')
+    eik_status rs = skip_remedy ? EIK_OK : sources(geom, c, static_cast<T*>(w.cells), queue && !alone);
+    if (rs == EIK_OK && alone && queue) rs = sources(geom_u, cu, nullptr, true);
+    if (rs != EIK_OK) return rs;
+    if (!queue && alone) {
         HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] {
             hipLaunchKernelGGL(k_seed_all_tiles, dim3(std::min((ntiles_u + kBlock - 1) / kBlock, 1024)), dim3(kBlock),
                                0, s, ntiles_u, w.q.tstamp, w.q.list_of(0));
             return hipGetLastError();
         }));
         launched += 1;
-    } else {
+    } else if (!queue) {
         HIP_TRY(detect(0));
         launched += 1;
     }
@@ -1133,40 +1162,45 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
     // solution takes 36 in all (45.5 -> 28.3 ms; 256^3 maze 13.2 -> 9.1 ms,
     // layered 192^3 5.4 -> 3.3 ms).
     int64_t n2 = 0;
-    eik_status rc = run_loop(
+    auto loop = [&](auto step, int64_t first, int64_t* steps, bool report) {
+        auto cnt = [&](int64_t t) { return counts(first + t); };
+        if (async || pageable)
+            return run_loop(step, cnt, kSub * kPad, cap, async, s, steps, w.ctl, pageable, report);
+        return run_tile_loop(step, cnt, kSub * kPad, first, cap, s, steps);
+    };
+    eik_status rc = loop(
         [&](int64_t t) {
             if (!alone) return visits(t, 0, false);
             return timed(prof, EIK_KERNEL_UPDATE,
                          [&] { return ku.update(iter_args(t, 0), geom_u, eT, inner_upd, gt, s); });
         },
-        counts, kSub * kPad, cap, async, s, &n2, w.ctl, pageable, alone);
+        0, &n2, alone);
     launched += n2;
+    Results res;
+    bool have = false;  // res holds the call's results
     if (rc == EIK_OK && !skip_remedy) {
         // STEP 3: detection adds to the list the next launch drains (what an
         // asynchronous update step left over is still in it), then the remedy
-        // loop.  A synchronous call reads the list's length first: after the
-        // correcting update step it is empty.
+        // loop.  A synchronous call reads the list's length first, with its
+        // results: after the correcting update step it is empty.
         HIP_TRY(detect(n2));
         launched += 1;
         int64_t n3 = 0;
-        bool open = true;
         if (!async && !alone) {
-            rc = list_total(counts(n2), kSub * kPad, s, pageable, open);
+            rc = read_results(w.ctl, w.blkstat, kMaxStatBlocks, pageable, s, res, counts(n2), kSub * kPad);
             if (rc != EIK_OK) return rc;
+            have = res.open == 0;
         }
-        if (open) {
-            rc = run_loop(
-                [&](int64_t t) {
-                    return visits(n2 + t, 1, t == 0);
-                },
-                [&](int64_t t) { return counts(n2 + t); }, kSub * kPad, cap, async, s, &n3, w.ctl, pageable);
+        if (!have) {
+            rc = loop([&](int64_t t) { return visits(n2 + t, 1, t == 0); }, n2, &n3, true);
             launched += n3;
         }
     }
     if (async) return rc;
-    Results res;
-    const eik_status rr = read_results(w.ctl, w.blkstat, kMaxStatBlocks, pageable, s, res);
-    if (rr != EIK_OK) return rr;
+    if (!have) {
+        const eik_status rr = read_results(w.ctl, w.blkstat, kMaxStatBlocks, pageable, s, res);
+        if (rr != EIK_OK) return rr;
+    }
     if (res.ctl.err & 1) return fail(EIK_ERR_INVALID_ARGUMENT, "F has negative or non-finite values");
     if (st) {
         *st = eik_stats{};
