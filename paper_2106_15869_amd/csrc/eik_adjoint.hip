@@ -386,8 +386,7 @@ __global__ __launch_bounds__(kBlock, (adj_blocks_per_cu<ND, Shape<ND, TX, TY, TZ
                 kmin = min(kmin, order_key(-ph[r]));
             }
         }
-        if (fm) atomicOr(&s_face, fm);
-        if (a.ordered && kmin != kNoKey) atomicMin(&s_kmin, kmin);
+        join_crossings<ND>(fm, kmin, &s_face, &s_kmin);
         __syncthreads();
         if (threadIdx.x < 7) {
             const int d = threadIdx.x;

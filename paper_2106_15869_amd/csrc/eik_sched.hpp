@@ -355,6 +355,34 @@ using ChunkMask = std::conditional_t<(NT <= 32 * 64), uint32_t, unsigned long lo
 // The lanes for which p holds, as a wave-uniform mask.
 __device__ __forceinline__ unsigned long long ballot64(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
+// Minimum over the wave's lanes (uniform): row shifts and row broadcasts, no LDS.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+    constexpr int kShr[4] = {0x111, 0x112, 0x114, 0x118};  // row_shr:1, 2, 4, 8
+    v = min(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(-1, static_cast<int>(v), kShr[0], 0xf, 0xf, false)));
+    v = min(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(-1, static_cast<int>(v), kShr[1], 0xf, 0xf, false)));
+    v = min(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(-1, static_cast<int>(v), kShr[2], 0xf, 0xf, false)));
+    v = min(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(-1, static_cast<int>(v), kShr[3], 0xf, 0xf, false)));
+    v = min(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(-1, static_cast<int>(v), 0x142, 0xa, 0xf, false)));  // row_bcast:15
+    v = min(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(-1, static_cast<int>(v), 0x143, 0xc, 0xf, false)));  // row_bcast:31
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
+// What a wave's lanes found when a visit ends: the faces they crossed (bit d)
+// and the smallest order key among them, joined in LDS with one atomic each (a
+// lane each, some 300 in a 3D tile, queued on one address for 2 us).
+template <int ND>
+__device__ __forceinline__ void join_crossings(int crossed, uint32_t key, int* s_face, uint32_t* s_key) {
+    int any = 0;
+#pragma unroll
+    for (int d = 0; d < 2 * ND; ++d) any |= __builtin_amdgcn_ballot_w64((crossed & (1 << d)) != 0) ? 1 << d : 0;
+    if (any == 0) return;
+    const uint32_t low = wave_min(key);
+    if ((threadIdx.x & 63) == 0) {
+        atomicOr(s_face, any);
+        atomicMin(s_key, low);
+    }
+}
+
 __device__ __forceinline__ uint32_t first_lane(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ unsigned long long first_lane(unsigned long long v) {
     return (static_cast<unsigned long long>(first_lane(static_cast<uint32_t>(v >> 32))) << 32) |

@@ -235,7 +235,7 @@ struct RemedyLds {
 // crossing key in LDS.  Returns the iterations run.
 template <typename T, int ND, int TX, int TY, int TZ, bool AN, typename Mask>
 __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T>& g, int t, int x0, int y0,
-                                            int z0, int open, T eps, int inner, bool ordered, uint32_t mask_in,
+                                            int z0, int open, T eps, int inner, uint32_t mask_in,
                                             const RemedyLds<T, Mask>& s, bool& pending) {
     using S = Shape<ND, TX, TY, TZ>;
     constexpr int WAVES = kBlock / 64;
@@ -345,7 +345,7 @@ __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T
     // write back what changed; a changed value that lies below the neighbour
     // across an open face crosses it
     int fm = 0, written = 0;
-    T kmin = inf;  // smallest value that crossed a face (order key of the pushes)
+    uint32_t kmin = kNoKey;  // order key of the smallest value that crossed a face
 #pragma unroll
     for (int r = 0; r < S::NPT; ++r) {
         const bool changed = cur[r] < old[r];
@@ -361,13 +361,10 @@ __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T
             if ((E & (1 << d)) && cur[r] < sphi[L + lds_offset<ND, TX, TY, TZ>(d)]) f |= 1 << d;
         if (f) {
             fm |= f;
-            kmin = tmin(kmin, cur[r]);
+            kmin = min(kmin, order_key(cur[r]));
         }
     }
-    if (fm) {
-        atomicOr(s.face, fm);
-        if (ordered) atomicMin(s.kmin, order_key(kmin));
-    }
+    join_crossings<ND>(fm, kmin, s.face, s.kmin);
     if (lane0) {
         if (evals) atomicAdd(s.evals, evals);
         if (written) atomicAdd(s.written, written);
@@ -722,7 +719,7 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
         const RemedyLds<T, Mask> rl{sphi, s_act, &s_mask, &s_face, &s_evals, &s_kmin, &s_unreached, &s_written};
         bool pending;
         const int it = remedy_visit<T, ND, TX, TY, TZ, AN>(a.cells, a.phi, g, t, x0, y0, z0, open, eps, inner,
-                                                           a.ordered, mask_in, rl, pending);
+                                                           mask_in, rl, pending);
         // scheduling, one lane per target tile (see the update kernel); the
         // targets are read by the next launch
         if (threadIdx.x < 7) {
