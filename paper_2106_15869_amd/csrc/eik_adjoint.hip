@@ -242,31 +242,40 @@ __global__ __launch_bounds__(kBlock, (adj_blocks_per_cu<ND, Shape<ND, TX, TY, TZ
     __shared__ int s_face;
     __shared__ uint32_t s_mask, s_key, s_kmin;
     const uint32_t ntag = launch_tag(a);
+    const unsigned long long e0 = first_entry(a);
     const int n = list_open(a, s_len);
     launch_stats(a, n);
     const int k = blockIdx.x & (kSub - 1);
     const int len = s_len[k];
     if (static_cast<int>(blockIdx.x) / kSub >= len) return;  // no first entry: none at all
-    const uint32_t thr = threadIdx.x < 64 ? sampled_threshold(a, s_len, n) : 0u;
+    const bool all = !a.ordered || n <= a.order_aim;  // the launch takes every tile listed
+    const uint32_t thr = !all && threadIdx.x < 64 ? sampled_threshold(a, s_len, n) : kNoKey;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool lane0 = (threadIdx.x & 63) == 0;
     int nx_, ny_, nz_, L0;
     node_loc<ND, TX, TY, TZ>(threadIdx.x, nx_, ny_, nz_, L0);
     unsigned long long visits = 0;
     for (;;) {
-        if (threadIdx.x == 0) {
-            const int tt = next_tile(a, k, len, visits == 0, thr, ntag, s_key);
-            if (tt >= 0) {
-                s_mask = a.mask_cur[tt];
-                a.mask_cur[tt] = 0u;
+        int t;
+        if (visits == 0 && all) {
+            t = static_cast<int>(static_cast<uint32_t>(e0));
+            if (threadIdx.x == 0) {
+                if (a.ordered) a.key_cur[t] = kNoKey;  // the tile leaves the list
+                s_key = static_cast<uint32_t>(e0 >> 32);
             }
+        } else {
+            if (threadIdx.x == 0) s_slot = next_tile(a, k, len, visits == 0, thr, ntag, s_key);
+            __syncthreads();
+            t = s_slot;
+            if (t < 0) break;
+        }
+        if (threadIdx.x == 0) {
+            // written by the previous launch; no writer during this one
+            s_mask = a.mask_cur[t];
+            a.mask_cur[t] = 0u;
             s_kmin = kNoKey;
             s_face = 0;
-            s_slot = tt;
         }
-        __syncthreads();
-        const int t = s_slot;
-        if (t < 0) break;
         ++visits;
         const Inst<T> g = inst_of(bg, t);
         const int lt = t - g.tile_base;

@@ -122,14 +122,18 @@ __device__ __forceinline__ int neighbour_tile(const Inst<T>& g, int t, int d) {
 
 // Tag chain: launch with slot p reads tag[p] and stores tag[p] + 1 into
 // tag[p ^ 1]; tiles it schedules are claimed with tag[p] + 1.
+// The last workgroup of a launch keeps its books: it is the one most likely to
+// have no tile to visit, so that nobody waits for its reads of the control
+// block.
+__device__ __forceinline__ bool book_keeper() { return blockIdx.x == gridDim.x - 1; }
 __device__ __forceinline__ uint32_t launch_tag(const Sched& a) {
     const uint32_t tag = static_cast<uint32_t>(a.ctl->tag[a.tag_slot]);
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl->tag[a.tag_slot ^ 1] = static_cast<int>(tag + 1);
+    if (book_keeper() && threadIdx.x == 0) a.ctl->tag[a.tag_slot ^ 1] = static_cast<int>(tag + 1);
     return tag + 1;
 }
 
 __device__ __forceinline__ void launch_stats(const Sched& a, int n) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (book_keeper() && threadIdx.x == 0) {
         const unsigned long long un = static_cast<unsigned long long>(n);
         if (n > 0) {
             if (a.phase == 0) {
@@ -180,7 +184,7 @@ __device__ __forceinline__ void push_keyed(const Sched& a, int t, uint32_t tag, 
 // Clear the counters of the list two launches ahead (nobody reads or writes
 // them during this launch) and return the total length of the current list.
 __device__ __forceinline__ int list_open(const Sched& a, int* s_len) {
-    if (blockIdx.x == 0 && threadIdx.x < kSub) {
+    if (book_keeper() && threadIdx.x < kSub) {
         a.zero_count[threadIdx.x * kPad] = 0;
         a.zero_fetch[threadIdx.x * kPad] = 0;
     }
@@ -193,8 +197,7 @@ __device__ __forceinline__ int list_open(const Sched& a, int* s_len) {
 }
 
 // Ordered: the largest key a launch takes, so that it visits about order_aim
-// of its n tiles, or n / kListShare if that is more -- all of them if there are
-// no more than order_aim.  The quantile of 64 listed keys, spread over the
+// of its n tiles (more than order_aim), or n / kListShare if that is more.  The quantile of 64 listed keys, spread over the
 // sub-lists: every workgroup draws the same sample (one 8-byte load per lane)
 // and ranks it without LDS.  The count is off by some 6 % of n, which costs
 // nothing.  At least one tile is taken: the one whose entry has the threshold's
@@ -207,7 +210,6 @@ __device__ __forceinline__ int list_open(const Sched& a, int* s_len) {
 // where nobody else added to the list there; without the share it took 28.8).
 constexpr int kListShare = 8;
 __device__ __forceinline__ uint32_t sampled_threshold(const Sched& a, const int* s_len, int n) {
-    if (!a.ordered || n <= a.order_aim) return kNoKey;
     const int lane = threadIdx.x & 63;
     const int k = lane & (kSub - 1), len = s_len[k];
     const int64_t e = static_cast<int64_t>(lane / kSub) * len / (64 / kSub);
@@ -238,6 +240,16 @@ __device__ __forceinline__ int fetch_index(const TList& L, int k, int len, bool 
     if (first) return static_cast<int>(blockIdx.x) / kSub;
     if (len <= fixed) return len;
     return fixed + atomicAdd(L.fetch + k * kPad, 1);
+}
+
+// A workgroup's first entry: its index is fixed, so it is read in the round of
+// the list lengths (an entry past the sub-list's end is not used: the grid has
+// no more workgroups than tiles, rounded up, and a sub-list room for more), by
+// every lane, so that no broadcast stands before the first visit.
+__device__ __forceinline__ unsigned long long first_entry(const Sched& a) {
+    const unsigned long long v = a.cur.data[static_cast<size_t>(blockIdx.x & (kSub - 1)) * a.cur.cap + blockIdx.x / kSub];
+    return (static_cast<unsigned long long>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32))) << 32) |
+           static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v)));
 }
 
 // The next tile a workgroup visits (lane 0; -1 when its sub-list k of `len`

@@ -690,19 +690,30 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
     __shared__ uint32_t s_key, s_kmin;
     __shared__ int s_unreached;
     const uint32_t ntag = launch_tag(a);
+    const unsigned long long e0 = first_entry(a);
     const int n = list_open(a, s_len);
     launch_stats(a, n);
     const int k = blockIdx.x & (kSub - 1);
     const int len = s_len[k];
     if (static_cast<int>(blockIdx.x) / kSub >= len) return;  // no first entry: none at all
-    const uint32_t thr = threadIdx.x < 64 ? sampled_threshold(a, s_len, n) : 0u;
+    const bool all = !a.ordered || n <= a.order_aim;  // the launch takes every tile listed
+    const uint32_t thr = !all && threadIdx.x < 64 ? sampled_threshold(a, s_len, n) : kNoKey;
     unsigned long long evals = 0, early = 0, inner_sum = 0, written = 0, visits = 0;
     for (;;) {
-        if (threadIdx.x == 0) s_slot = next_tile(a, k, len, visits == 0, thr, ntag, s_key);
-        __syncthreads();
-        const int t = s_slot;
-        __syncthreads();
-        if (t < 0) break;
+        int t;
+        if (visits == 0 && all) {
+            t = static_cast<int>(static_cast<uint32_t>(e0));
+            if (threadIdx.x == 0) {
+                if (a.ordered) a.key_cur[t] = kNoKey;  // the tile leaves the list
+                s_key = static_cast<uint32_t>(e0 >> 32);
+            }
+        } else {
+            if (threadIdx.x == 0) s_slot = next_tile(a, k, len, visits == 0, thr, ntag, s_key);
+            __syncthreads();
+            t = s_slot;
+            __syncthreads();
+            if (t < 0) break;
+        }
         ++visits;
         const Inst<T> g = inst_of(bg, t);
         const int lt = t - g.tile_base;
