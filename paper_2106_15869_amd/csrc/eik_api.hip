@@ -288,17 +288,32 @@ static eik_status solve_nodelist(const Problem& P, const T* F, const Spacing<T>&
     auto counts = [&](int64_t t) { return w.seg[t & 1].count; };
     const int per_iter = det ? 2 : 1;
 
+    // Deterministic calls without a launch budget run short lists in one launch
+    // of many iterations (k_node_run) before each ordinary iteration.  The
+    // longest front is some 1.7 sides in 2D and one face in 3D, the remedy's
+    // lists a tenth of the nodes and more: grids whose lists would mostly be too
+    // long do without, as each would pay an empty launch (4 us) for nothing.
+    constexpr int kRun = 64;
+    const bool can_run = det && !fim && o.max_iters <= 0;
+    const bool run2 = can_run && P.n <= (P.g.nd == 2 ? 1500000 : 100000), run3 = can_run && P.n <= 30000;
+    auto run_some = [&](int64_t t, bool step2, int kind) {
+        return timed(prof, kind, [&] { return launch_node_run<T>(P.g, iter_args(t, t == 0), hT, eT, step2, kRun, s); });
+    };
     // STEP 2 (FIM: its update with the neighbour check, two launches per iteration)
     int64_t n2 = 0, n3 = 0;
     eik_status rc = run_loop(
         [&](int64_t t) {
+            if (run2) {
+                const hipError_t e = run_some(t, true, EIK_KERNEL_UPDATE);
+                if (e != hipSuccess) return e;
+            }
             return timed(prof, EIK_KERNEL_UPDATE, [&] {
                 return fim ? launch_fim<T>(P.g, iter_args(t, t == 0), hT, eT, s)
                            : launch_step2<T>(P.g, iter_args(t, t == 0), hT, eT, det, s);
             });
         },
-        counts, kNodeSegs, cap, async, s, &n2, w.ctl, pageable);
-    launched += (fim ? 2 : per_iter) * n2;
+        counts, kNodeSegs, cap, async, s, &n2, w.ctl, pageable, true, run2 ? 2 : 8);
+    launched += ((fim ? 2 : per_iter) + (run2 ? 1 : 0)) * n2;
     if (rc == EIK_OK && !fim && !(o.flags & EIK_FLAG_SKIP_REMEDY)) {
         // STEP 3a: whole-grid check into list 0
         HIP_TRY(timed(prof, EIK_KERNEL_DETECT,
@@ -307,11 +322,15 @@ static eik_status solve_nodelist(const Problem& P, const T* F, const Spacing<T>&
         // STEP 3b: remedy loop
         rc = run_loop(
             [&](int64_t t) {
+                if (run3) {
+                    const hipError_t e = run_some(t, false, EIK_KERNEL_REMEDY);
+                    if (e != hipSuccess) return e;
+                }
                 return timed(prof, EIK_KERNEL_REMEDY,
-                             [&] { return launch_remedy<T>(P.g, iter_args(t, t == 0), hT, eT, det, s); });
+                             [&] { return launch_remedy<T>(P.g, iter_args(t, t == 0 && !run3), hT, eT, det, s); });
             },
-            counts, kNodeSegs, cap, async, s, &n3, w.ctl, pageable);
-        launched += per_iter * n3;
+            counts, kNodeSegs, cap, async, s, &n3, w.ctl, pageable, true, run3 ? 2 : 8);
+        launched += (per_iter + (run3 ? 1 : 0)) * n3;
     }
     if (async) return rc;
     Results res;

@@ -149,9 +149,11 @@ inline hipError_t timed(Profiler& p, int kind, Fn fn) {
 // With `pageable` the lengths are copied into a stack buffer after each
 // chunk and the host waits for them before enqueuing the next chunk (no
 // pinned memory, no events; the device idles while the host enqueues).
+// (chunk: even, as list parity repeats.)
 template <typename StepFn, typename CountsFn>
 inline eik_status run_loop(StepFn step, CountsFn counts, int nseg, int64_t max_iters, bool async,
-                           hipStream_t s, int64_t* steps, Ctl* ctl, bool pageable = false, bool report = true) {
+                           hipStream_t s, int64_t* steps, Ctl* ctl, bool pageable = false, bool report = true,
+                           int64_t chunk = 8) {
     if (async) {
         for (int64_t t = 0; t < max_iters; ++t) HIP_TRY(step(t));
         if (report) HIP_TRY(launch_loop_status(ctl, counts(max_iters), nseg, s));
@@ -180,7 +182,6 @@ inline eik_status run_loop(StepFn step, CountsFn counts, int nseg, int64_t max_i
     }
     HostSlots& hs = host_slots();
     if (!hs.ok) return fail(EIK_ERR_DEVICE, "pinned host buffer allocation failed");
-    const int64_t chunk = 8;  // even: list parity repeats
     auto total = [&](int slot) {
         long long sum = 0;
         const int* w = hs.words + slot * (HostSlots::kWords / 2);

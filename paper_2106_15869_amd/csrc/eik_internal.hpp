@@ -197,6 +197,11 @@ hipError_t launch_clear(const ClearPlan& c, hipStream_t s);
 template <typename T>
 hipError_t launch_apply_local(const GridDims& g, const T* F, const T* phi, const Spacing<T>& h, T* out,
                               hipStream_t s);
+// Up to `iters` iterations of a synchronous-read loop in one launch, while its
+// list is short (nothing else is done to a list that is empty or long).
+template <typename T>
+hipError_t launch_node_run(const GridDims& g, const NodeIter<T>& it, const Spacing<T>& h, T eps, bool step2, int iters,
+                           hipStream_t s);
 template <typename T>
 hipError_t launch_fim(const GridDims& g, const NodeIter<T>& it, const Spacing<T>& h, T eps, hipStream_t s);
 hipError_t launch_reset_counters(Ctl* ctl, hipStream_t s);

@@ -548,6 +548,195 @@ __global__ __launch_bounds__(kBlock) void k_fim_check(NodeIter<T> a, GridDims gd
     app.publish(a.next);
 }
 
+// ---------------------------------------------------------------------------
+// Synchronous reads, short lists: many iterations in one launch
+// ---------------------------------------------------------------------------
+// One workgroup runs up to `iters` iterations of STEP 2 or of the remedy loop
+// while the list holds 1 .. kRunMost nodes, and leaves what remains as the
+// current list of the same iteration parity.  An iteration of two launches
+// (every active node evaluated, then applied) takes 11 to 14 us however short
+// the list is; here the two phases are two barriers apart, a node's value stays
+// in the lane that evaluated it, and what is left is three memory round trips:
+// neighbour values, neighbour labels, claims, each issued for all neighbours
+// together.  Reads are synchronous as there, so values and counts are the same;
+// only the order of the list differs.  Labels are read past the L1 (its lines
+// are not told of atomics); values and list entries are stored and loaded by
+// one CU, whose L1 is written through.
+constexpr int kRunBlock = 1024;
+constexpr int kRunPer = 2;                        // list entries per lane
+constexpr int kRunMost = kRunBlock * kRunPer;
+
+__device__ __forceinline__ uint32_t label_word(const uint8_t* lab, int i) {
+    return __hip_atomic_load(reinterpret_cast<const uint32_t*>(lab + (i & ~3)), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+template <typename T, int ND, bool STEP2>
+__global__ __launch_bounds__(kRunBlock) void k_node_run(NodeIter<T> a, GridDims gd, Spacing<T> sp, T eps, int iters) {
+    __shared__ int s_pref[G + 1];
+    __shared__ int s_scan[G / 64];
+    __shared__ int s_cnt[2];
+    __shared__ int s_w;
+    const Grid g = make_grid(gd);
+    const T inf = pos_inf<T>();
+    const int tid = threadIdx.x;
+    // prefix of the segment lengths (waves 0 .. G / 64 - 1)
+    int c = 0, incl = 0;
+    if (tid < G) {
+        c = a.cur.count[tid];
+        incl = wave_incl_scan(c);
+        if (lane_id() == 63) s_scan[tid >> 6] = incl;
+    }
+    if (tid == 0) {
+        s_w = 0;
+        s_cnt[0] = s_cnt[1] = 0;
+    }
+    __syncthreads();
+    int n = 0;
+    for (int w = 0; w < G / 64; ++w) {
+        if (tid < G && w == (tid >> 6)) s_pref[tid] = n + incl - c;
+        n += s_scan[w];
+    }
+    if (tid == 0) s_pref[G] = n;
+    __syncthreads();
+    if (!STEP2 && a.first && tid == 0) a.ctl->remedy_init = static_cast<unsigned long long>(n);
+    if (n == 0 || n > kRunMost) return;
+    const uint32_t tag = static_cast<uint32_t>(a.ctl->tag[a.tag_slot]);
+    unsigned long long evals = 0, most = 0;
+    int written = 0, it = 0;
+    int* buf[2] = {a.cur.data, a.next.data};  // iteration it reads buf[it & 1], the first one by segments
+    for (; it < iters && n > 0 && n <= kRunMost; ++it) {
+        evals += static_cast<unsigned long long>(n);
+        if (static_cast<unsigned long long>(n) > most) most = static_cast<unsigned long long>(n);
+        const int* in = buf[it & 1];
+        int* out = buf[(it + 1) & 1];
+        int id[kRunPer];
+        T v[kRunPer], old[kRunPer];
+#pragma unroll
+        for (int r = 0; r < kRunPer; ++r) {
+            const int k = tid + r * kRunBlock;
+            id[r] = -1;
+            if (r * kRunBlock >= n || k >= n) continue;
+            const int i = it == 0 ? seg_entry<G>(a.cur, s_pref, k) : in[k];
+            int x, y, z;
+            decode<ND>(g, i, x, y, z);
+            id[r] = i;
+            old[r] = a.phi[i];
+            v[r] = eval_node<T, ND>(a.phi, a.F, g, i, x, y, z, sp);
+        }
+        if (tid == 0) s_cnt[(it + 1) & 1] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kRunPer; ++r) {
+            if (r * kRunBlock >= n) break;
+            const int i = id[r];
+            int nb[6];
+            uint32_t valid = 0, mask = 0;
+            bool self = false;
+            // the nodes whose neighbours may join: converged ones in STEP 2,
+            // changed ones in the remedy
+            bool spread = false;
+            if (i >= 0) {
+                if (STEP2) {
+                    if (v[r] < inf && old[r] - v[r] <= eps) {
+                        spread = true;
+                    } else if (v[r] < inf) {
+                        if (v[r] < old[r]) {
+                            a.phi[i] = v[r];
+                            ++written;
+                        }
+                        self = true;
+                    }
+                } else if (v[r] < old[r] - eps) {
+                    a.phi[i] = v[r];
+                    ++written;
+                    spread = true;
+                }
+            }
+            if (spread) {
+                int x, y, z;
+                decode<ND>(g, i, x, y, z);
+                neighbour_slots<ND>(g, i, x, y, z, nb, valid);
+                uint32_t lw[2 * ND];
+                T f[2 * ND];
+#pragma unroll
+                for (int j = 0; j < 2 * ND; ++j) {
+                    const int q = (valid >> j) & 1u ? nb[j] : i;
+                    lw[j] = label_word(a.lab, q) >> ((q & 3) * 8) & 0xffu;
+                    f[j] = STEP2 ? a.F[q] : T(1);
+                }
+                uint32_t was[2 * ND];
+#pragma unroll
+                for (int j = 0; j < 2 * ND; ++j) {
+                    const int q = nb[j];
+                    const bool want = ((valid >> j) & 1u) &&
+                                      (STEP2 ? lw[j] == L_FAR && f[j] > T(0) : lw[j] != L_FIXED);
+                    was[j] = STEP2 ? 0xffu : ~0u;
+                    if (!want) continue;
+                    if (STEP2) {
+                        // FAR -> ACTIVE: a node that is FAR in this phase is FAR or
+                        // ACTIVE until its end, so setting the bit claims it once
+                        static_assert(L_FAR == 0u && L_ACTIVE == 1u, "one bit");
+                        was[j] = __hip_atomic_fetch_or(reinterpret_cast<uint32_t*>(a.lab + (q & ~3)),
+                                                       L_ACTIVE << ((q & 3) * 8), __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_WORKGROUP) >> ((q & 3) * 8) & 0xffu;
+                    } else {
+                        was[j] = __hip_atomic_fetch_max(a.stamp + q, tag + it, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                }
+                if (!STEP2)
+                    self = __hip_atomic_fetch_max(a.stamp + i, tag + it, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_WORKGROUP) < tag + it;
+#pragma unroll
+                for (int j = 0; j < 2 * ND; ++j)
+                    if (STEP2 ? was[j] == L_FAR : was[j] < tag + it) mask |= 1u << j;
+            }
+            // label of a node that leaves the list: CONV, or back to FAR with
+            // nothing finite upwind
+            if (STEP2 && i >= 0 && !self) {
+                const int delta = spread ? static_cast<int>(L_CONV) - static_cast<int>(L_ACTIVE)
+                                         : static_cast<int>(L_FAR) - static_cast<int>(L_ACTIVE);
+                __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(a.lab + (i & ~3)),
+                                       static_cast<uint32_t>(delta) << ((i & 3) * 8), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            const int add = __popc(mask) + (self ? 1 : 0);
+            const int upto = wave_incl_scan(add);
+            const int total = __shfl(upto, 63, 64);
+            if (total == 0) continue;
+            int base = 0;
+            if (lane_id() == 63) base = atomicAdd(&s_cnt[it & 1], total);
+            int at = __shfl(base, 63, 64) + upto - add;
+#pragma unroll
+            for (int j = 0; j < 2 * ND; ++j)
+                if (mask & (1u << j)) out[at++] = nb[j];
+            if (self) out[at] = i;
+        }
+        __syncthreads();
+        n = s_cnt[it & 1];
+        __syncthreads();
+    }
+    // what remains: flat in buf[it & 1], read by segments of `cap` entries
+    if (it & 1)
+        for (int k = tid; k < n; k += kRunBlock) buf[0][k] = buf[1][k];
+    if (tid < G) a.cur.count[tid] = max(0, min(a.cur.cap, n - tid * a.cur.cap));
+    if (written) atomicAdd(&s_w, written);
+    __syncthreads();
+    if (tid == 0) {
+        a.blkstat[(STEP2 ? SF_WRITTEN2 : SF_WRITTEN3) * G] += static_cast<unsigned long long>(s_w);
+        if (STEP2) {
+            a.ctl->iters2 += static_cast<unsigned long long>(it);
+            a.ctl->evals2 += evals;
+            if (most > a.ctl->max_active) a.ctl->max_active = most;
+        } else {
+            a.ctl->iters3 += static_cast<unsigned long long>(it);
+            a.ctl->evals_rem += evals;
+            a.ctl->tag[a.tag_slot] = static_cast<int>(tag + it);
+        }
+    }
+}
+
 // One dense pass: a lane owns an index of a plane (a row in 2D) and walks
 // `steps` planes along the outer axis, keeping the values behind and ahead in
 // registers, so that a node costs one new value and one speed from memory (the
@@ -812,6 +1001,20 @@ hipError_t launch_apply_local(const GridDims& g, const T* F, const T* phi, const
 }
 
 template <typename T>
+hipError_t launch_node_run(const GridDims& g, const NodeIter<T>& it, const Spacing<T>& h, T eps, bool step2, int iters,
+                           hipStream_t s) {
+    const dim3 one(1), block(kRunBlock);
+    if (g.nd == 2) {
+        if (step2) hipLaunchKernelGGL((k_node_run<T, 2, true>), one, block, 0, s, it, g, h, eps, iters);
+        else hipLaunchKernelGGL((k_node_run<T, 2, false>), one, block, 0, s, it, g, h, eps, iters);
+    } else {
+        if (step2) hipLaunchKernelGGL((k_node_run<T, 3, true>), one, block, 0, s, it, g, h, eps, iters);
+        else hipLaunchKernelGGL((k_node_run<T, 3, false>), one, block, 0, s, it, g, h, eps, iters);
+    }
+    return hipGetLastError();
+}
+
+template <typename T>
 hipError_t launch_fim(const GridDims& g, const NodeIter<T>& it, const Spacing<T>& h, T eps, hipStream_t s) {
     if (g.nd == 2) {
         hipLaunchKernelGGL((k_fim_update<T, 2>), dim3(G), dim3(kBlock), 0, s, it, g, h, eps);
@@ -856,6 +1059,8 @@ hipError_t launch_loop_status(Ctl* ctl, const int* counts, int nseg, hipStream_t
                                          bool, hipStream_t);                                       \
     template hipError_t launch_apply_local<T>(const GridDims&, const T*, const T*, const Spacing<T>&, \
                                               T*, hipStream_t);                                    \
+    template hipError_t launch_node_run<T>(const GridDims&, const NodeIter<T>&, const Spacing<T>&, T, bool, int, \
+                                           hipStream_t);                                           \
     template hipError_t launch_fim<T>(const GridDims&, const NodeIter<T>&, const Spacing<T>&, T, hipStream_t);
 
 EIK_INST(float)
