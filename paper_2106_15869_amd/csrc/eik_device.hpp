@@ -230,6 +230,47 @@ __device__ __forceinline__ T godunov_aniso(T a0, T a1, T a2, T H0, T H1, T H2) {
     return phi;
 }
 
+// godunov_aniso in 2D with everything that depends on the node alone formed
+// once, the same value bit for bit: H_k, w_k, A = w_0 + w_1 (the sum does not
+// depend on the order) and its rounded reciprocal, by which the last quotient is
+// formed and corrected by its exact remainder (correctly rounded unless A's
+// digits are all ones, which fits() excludes).  In the loop of a tile visit the
+// general form divides three to five times.
+template <typename T>
+struct AnisoNode {
+    T H0, H1, w0, w1, A, rA;
+    __device__ __forceinline__ void set(T d0, T d1, T f) {
+        H0 = d0 / f;
+        H1 = d1 / f;
+        w0 = T(1) / (H0 * H0);
+        w1 = T(1) / (H1 * H1);
+        A = w0 + w1;
+        rA = T(1) / A;
+    }
+    // whether the range leaves room for squares, discriminants and remainders
+    __device__ __forceinline__ bool fits() const {
+        const T lo = sizeof(T) == 4 ? T(0x1p-30) : T(0x1p-200), hi = sizeof(T) == 4 ? T(0x1p+30) : T(0x1p+200);
+        bool ones;
+        if constexpr (sizeof(T) == 4) ones = (__float_as_uint(A) & 0x7fffffu) == 0x7fffffu;
+        else ones = (static_cast<unsigned long long>(__double_as_longlong(A)) & 0xfffffffffffffull) == 0xfffffffffffffull;
+        return H0 > lo && H0 < hi && H1 > lo && H1 < hi && !ones;
+    }
+    // (a barrier, f = 0, gives +inf or NaN, which is below nothing)
+    __device__ __forceinline__ T solve(T a0, T a1) const {
+        const bool swap = a1 < a0;
+        const T lo = vmin(a0, a1), hi = vmax(a0, a1);
+        const T phi1 = lo + (swap ? H1 : H0);
+        const T w = swap ? w0 : w1;
+        const T b = hi - lo;
+        const T B = w * b;
+        const T C = T(-1) + B * b;
+        const T x = B + sqrt_mid(vmax(B * B - A * C, T(0)));
+        const T q = x * rA;
+        const T phi2 = lo + __builtin_elementwise_fma(__builtin_elementwise_fma(-A, q, x), rA, q);
+        return phi1 > hi ? phi2 : phi1;
+    }
+};
+
 // G_i from the per-axis minima (dims order) and the node's speed.
 template <typename T, int ND>
 __device__ __forceinline__ T local_solve(T a0, T a1, T a2, T f, const Spacing<T>& sp) {

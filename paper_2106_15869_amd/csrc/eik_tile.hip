@@ -263,6 +263,8 @@ __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T
     int nx, ny, nz, L0;
     node_loc<ND, TX, TY, TZ>(threadIdx.x, nx, ny, nz, L0);
     T cur[S::NPT], old[S::NPT], hh[S::NPT];
+    constexpr bool AN2 = AN && ND == 2;
+    AnisoNode<T> an[AN2 ? S::NPT : 1];
     int nfree[S::NPT];
     Mask todo = 0;  // chunks to evaluate (the wave looks at its own)
     bool unreached = false, ends = false;
@@ -277,7 +279,12 @@ __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T
         hh[r] = hv[r] * hv[r];
         nfree[r] = __popcll(ballot64(fr));
         unreached |= fr && !(cur[r] < inf);
-        ends |= fr && !mid_range(hv[r]);
+        if constexpr (AN2) {
+            an[r].set(g.d[0], g.d[1], hv[r]);
+            ends |= fr && !an[r].fits();
+        } else {
+            ends |= fr && !mid_range(hv[r]);
+        }
         if (ballot64(fr && ((m & kAllFaces) || (E & static_cast<int>(m))))) todo |= Mask(1) << (r * WAVES + wave);
     }
     if (ballot64(unreached) && lane0) *s.unreached = 1;
@@ -327,7 +334,8 @@ __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T
                 T(&v)[2 * ND] = nv[AHEAD ? r : 0];
                 if (!AHEAD) load_nb<T, ND, TX, TY, TZ>(sphi, L, v);
                 T pt;
-                if constexpr (decltype(mid_c)::value) pt = eval_nb_mid<T, ND>(v, hv[r], hh[r]);
+                if constexpr (decltype(mid_c)::value && AN2) pt = an[r].solve(vmin(v[2], v[3]), vmin(v[0], v[1]));
+                else if constexpr (decltype(mid_c)::value) pt = eval_nb_mid<T, ND>(v, hv[r], hh[r]);
                 else pt = eval_nb<T, ND, AN>(v, hv[r], g);
                 const bool drop = pt < cur[r] - eps;
                 cur[r] = drop ? pt : cur[r];
@@ -339,7 +347,7 @@ __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T
             __syncthreads();
         }
     };
-    if constexpr (AN) iterate(std::false_type{});
+    if constexpr (AN && !AN2) iterate(std::false_type{});
     else if (ballot64(ends) == 0) iterate(std::true_type{});
     else iterate(std::false_type{});
     // write back what changed; a changed value that lies below the neighbour

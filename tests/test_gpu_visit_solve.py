@@ -38,6 +38,12 @@ def test_short_and_general_solve_agree(dims, tile, dtype):
     for k in (shift, 1.0 / shift):
         other = eik.solve(Fd, 0.25 * k, src, tile=tile).cpu().numpy()
         np.testing.assert_array_equal(other, (mid * np.array(k, dtype=dtype)).astype(dtype))
+    if len(dims) == 2 and tile is None:  # per-axis spacing (default tiles), scaled alike
+        sp = (0.25, 0.4)
+        an = eik.solve(Fd, None, src, spacing=sp).cpu().numpy()
+        for k in (shift, 1.0 / shift):
+            other = eik.solve(Fd, None, src, spacing=(sp[0] * k, sp[1] * k)).cpu().numpy()
+            np.testing.assert_array_equal(other, (an * np.array(k, dtype=dtype)).astype(dtype))
     ref = oracle.fmm(F.astype(np.float64), 0.25, src)
     live = np.isfinite(ref)
     np.testing.assert_array_equal(live, np.isfinite(mid))
