@@ -204,7 +204,6 @@ hipError_t launch_node_run(const GridDims& g, const NodeIter<T>& it, const Spaci
                            hipStream_t s);
 template <typename T>
 hipError_t launch_fim(const GridDims& g, const NodeIter<T>& it, const Spacing<T>& h, T eps, hipStream_t s);
-hipError_t launch_reset_counters(Ctl* ctl, hipStream_t s);
 hipError_t launch_ctl_init(Ctl* ctl, hipStream_t s);
 // After the last budgeted launch of an asynchronous loop: sums the `nseg`
 // length words of the list the next launch would drain and records in

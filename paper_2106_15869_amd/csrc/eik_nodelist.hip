@@ -12,6 +12,8 @@
 //           drop form the Remedy list; k_remedy (or eval + apply): changed
 //           nodes take the new value and, with their neighbours, form the
 //           next Remedy list.
+//   k_node_run: many iterations of STEP 2 or the remedy loop in one launch
+//           (synchronous reads, short lists).
 // Lists are int32 node indices in per-workgroup segments (eik_seglist.hpp):
 // each wave compacts its items with a lane prefix sum and reserves room with
 // one LDS atomic.  Labels are bytes changed with word atomics.
@@ -790,10 +792,6 @@ __global__ __launch_bounds__(kBlock) void k_apply_local(GridDims gd, const T* __
     }
 }
 
-__global__ void k_reset_counters(Ctl* ctl) {
-    if (threadIdx.x < 4) ctl->cnt[threadIdx.x] = 0;
-}
-
 // Zero the whole control block (runs before any kernel of a solve).
 __device__ __forceinline__ void ctl_init(Ctl* ctl) {
     for (int k = 0; k < 4; ++k) ctl->cnt[k] = 0;
@@ -1023,11 +1021,6 @@ hipError_t launch_fim(const GridDims& g, const NodeIter<T>& it, const Spacing<T>
         hipLaunchKernelGGL((k_fim_update<T, 3>), dim3(G), dim3(kBlock), 0, s, it, g, h, eps);
         hipLaunchKernelGGL((k_fim_check<T, 3>), dim3(G), dim3(kBlock), 0, s, it, g, h, eps);
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_reset_counters(Ctl* ctl, hipStream_t s) {
-    hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(64), 0, s, ctl);
     return hipGetLastError();
 }
 

@@ -300,9 +300,8 @@ __device__ __forceinline__ void stat_add(unsigned long long* blkstat, int field,
 // ---------------------------------------------------------------------------
 // In-tile work lists
 // ---------------------------------------------------------------------------
-// Nodes of a tile are numbered n = (z * TY + y) * TX + x.  The inner
-// iterations of a visit work on an LDS list of node ids instead of sweeping
-// all nodes: iteration it drains list it & 1 (length cnt[it % 3]) and appends
+// Nodes of a tile are numbered n = (z * TY + y) * TX + x.  The update step
+// alone works on an LDS list of node ids: inner iteration it drains list it & 1 (length cnt[it % 3]) and appends
 // to list (it + 1) & 1; a per-list flag array keeps entries unique.  Only as
 // many waves as the list needs evaluate the local solver.
 template <int ND, int TX, int TY, int TZ>

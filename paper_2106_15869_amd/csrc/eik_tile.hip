@@ -2,15 +2,15 @@
 //
 // The grid is cut into tiles of TZ x TY x TX nodes.  A launch drains a list
 // of tiles with persistent workgroups (256 lanes, four wave64), one tile
-// visit at a time.  A visit stages the tile's values, labels and speeds plus
-// a one-cell halo in LDS (one round of global loads), runs the node rules of
-// Algorithm 2 for several inner iterations on an LDS list of nodes without
-// touching HBM, writes back what changed and schedules the tiles that have
-// to be visited next (eik_sched.hpp: sub-list queues, stamps, order keys).
+// visit at a time.  A visit stages the tile's values plus a one-cell halo in
+// LDS (one round of global loads), runs the node rules of Algorithm 2 for
+// several inner iterations without touching HBM, writes back what changed and
+// schedules the tiles that have to be visited next (eik_sched.hpp: sub-list
+// queues, stamps, order keys).
 //
 //   update step (STEP 2), default: from the sources outward, tile visits by
 //     the remedy rule below -- a node takes phi~ = G_i(phi) when that is
-//     lower and lists its neighbours -- lowest keys first.  Values settled
+//     lower and its neighbours are evaluated again -- lowest keys first.  Values settled
 //     from the wrong side are corrected while the front is near (early
 //     remedy) instead of after it has passed.
 //   update step alone (EIK_FLAG_SKIP_REMEDY; 3D with
@@ -23,13 +23,12 @@
 //   remedy detection (STEP 3, first part): one dense pass over all tiles;
 //     a tile with any node whose phi~ < phi - eps enters the remedy list.
 //   remedy loop (STEP 3): the remedy rule of Section 3.1.2 restricted to the
-//     tile: recompute the listed nodes, take the drops, list the in-tile
-//     neighbours below which a dropped value now lies for the next inner
-//     iteration, until the list is empty.  A tile enters with all nodes
-//     listed (first visit) or with the nodes on the faces whose neighbour tile
-//     changed; a drop on a tile face marks that face dirty in the tile across
-//     it and schedules it with the dropped value as its order key.  By
-//     default (ordered remedy) a launch visits only the lowest-key tiles of
+//     tile: evaluate the nodes, take the drops, evaluate again where a
+//     neighbour changed, until nothing does (remedy_visit).  A tile enters with
+//     all nodes to recheck (first visit) or with those on the faces whose
+//     neighbour tile changed; a drop on a tile face marks that face dirty in
+//     the tile across it and schedules it with the dropped value as its order
+//     key.  By default (ordered) a launch visits only the lowest-key tiles of
 //     its list and sends the others on to the next.
 // Values are updated in place within an inner iteration (a read racing with
 // an update sees either value, both upper bounds of the solution); tiles of
@@ -654,13 +653,8 @@ __global__ __launch_bounds__(kBlock) void k_tile_detect(TileIter<T> a, BatchGeom
 }
 
 // ---------------------------------------------------------------------------
-// STEP 3: remedy loop on tiles
+// Remedy visits: the correcting update step and the remedy loop
 // ---------------------------------------------------------------------------
-// The remedy rule restricted to the tile, on an LDS remedy list: a listed
-// node that drops takes the new value; its in-tile neighbours are listed for
-// the next iteration when the new value lies below theirs (otherwise their
-// update cannot change: the node is not upwind of them), and a face neighbour
-// below the halo value marks that face dirty in the tile across it.
 // Statistics of a workgroup's visits, by the loop it ran in.
 __device__ __forceinline__ void visit_stats(const Sched& a, unsigned long long evals, unsigned long long early,
                                             unsigned long long visits, unsigned long long inner,
