@@ -211,35 +211,35 @@ def replay(torch, eik, W):
     return rows
 
 
-def alg_bytes(kind, st, esz=4):
-    """Bytes the method must move for one kernel kind over a whole solve, in
-    the unit of the scope table: one local-solver evaluation reads the node's
-    F and phi (2 * esz; neighbour values come from the same staged tile), and
-    every value that changes is written once (esz).  Detection evaluates
-    every non-source node and writes nothing.  The update kernel also runs
-    the early remedy visits (3D): their evaluations count there (their
-    writes are not counted)."""
-    if kind == "update":
-        return 2 * esz * (st["evals_step2"] + st["evals_early"]) + esz * st["written_step2"]
-    if kind == "remedy":
-        return 2 * esz * st["evals_remedy"] + esz * st["written_step3"]
+def alg_bytes(kind, st, variant, tile_nodes, esz=4):
+    """Bytes the method must move for one kernel kind over a whole solve.  A
+    tile visit reads every node's cell value and phi once (2 * esz) however
+    many of its inner iterations evaluate the node, and writes every value
+    that changed (esz); a node-list evaluation reads the node's F and phi.
+    Detection evaluates every non-source node and writes nothing."""
     if kind == "detect":
         return 2 * esz * st["evals_detect"]
-    return None
+    step = {"update": "step2", "remedy": "step3"}.get(kind)
+    if step is None:
+        return None
+    if variant == "tile":
+        read = st[f"tile_visits_{step}"] * tile_nodes
+    else:
+        read = st["evals_step2"] if kind == "update" else st["evals_remedy"]
+    return 2 * esz * read + esz * st[f"written_{step}"]
 
 
 def staged_bytes(kind, st, variant, n_nodes, tile_nodes, esz=4):
     """Bytes a kernel kind stages over a whole solve (second view): a tile
-    visit reads every node's F and phi (2 * esz) and label (1 B) into LDS and
-    writes back the changed values (esz, plus the label in the update step);
+    visit reads every node's cell value and phi (2 * esz) with the phi of a
+    one-cell halo and writes back the changed values (esz);
     a node-list evaluation adds about 9 B of list and label traffic."""
     if kind == "detect":
-        return n_nodes * (2 * esz + 1)
+        return n_nodes * 2 * esz
     if variant == "tile":
-        if kind == "update":
-            return st["tile_visits_step2"] * tile_nodes * (2 * esz + 1) + st["written_step2"] * (esz + 1)
-        if kind == "remedy":
-            return st["tile_visits_step3"] * tile_nodes * (2 * esz + 1) + st["written_step3"] * esz
+        step = {"update": "step2", "remedy": "step3"}.get(kind)
+        if step:
+            return st[f"tile_visits_{step}"] * esz * (tile_nodes + 10 ** 3) + st[f"written_{step}"] * esz
     else:
         if kind == "update":
             return st["evals_step2"] * (2 * esz + 9) + st["written_step2"] * esz
@@ -550,10 +550,11 @@ def main():
     tile_nodes = 8 * 8 * 8
     dom_ms = kernels[dom]["ms"]
     dom_launches = max(kernels[dom]["launches"], 1)
-    b_alg = alg_bytes(dom, pst)
+    b_alg = alg_bytes(dom, pst, a.variant, tile_nodes)
     b_staged = staged_bytes(dom, pst, a.variant, P.n, tile_nodes)
     achieved = b_alg / (dom_ms / 1e3) / 1e9 if b_alg else None
-    kname = f"{'k_tile_' if a.variant == 'tile' else 'k_'}{dom}"
+    # (the tile schedule's update step runs the remedy visits' kernel)
+    kname = f"k_tile_{'remedy' if dom == 'update' else dom}" if a.variant == "tile" else f"k_{dom}"
     ksym = f"{kname}IfLi3ELi8ELi8ELi8ELb0E" if a.variant == "tile" else f"{kname}IfLi3E"
     code_hash = kernel_code_hash(ksym)
     floor = 28 * P.n  # 3 evaluations x 8 B + one 4 B write per node
@@ -565,14 +566,15 @@ def main():
         "unit": "GB/s",
         "frac": achieved / HBM_PEAK_GBS if achieved else None,
         "traffic": measured_traffic(kname, code_hash),
-        "bytes_rule": "8 B per local-solver evaluation (F, phi) + 4 B per changed value",
+        "bytes_rule": "tile visits x 512 nodes x 8 B (cell, phi) + 4 B per changed value" if a.variant == "tile"
+                      else "8 B per local-solver evaluation (F, phi) + 4 B per changed value",
         "launches": dom_launches,
         "avg_launch_us": dom_ms * 1e3 / dom_launches,
         "algorithmic_bytes_per_launch": b_alg / dom_launches if b_alg else None,
         "kernel_code_sha16": code_hash,
         "staged": {"bytes_per_launch": b_staged / dom_launches if b_staged else None,
                    "achieved_GBs": b_staged / (dom_ms / 1e3) / 1e9 if b_staged else None,
-                   "rule": "tile visits x 512 nodes x 9 B (F, phi, label) + changed values x 4 B"},
+                   "rule": "tile visits x (512 cells + 1000 phi) x 4 B + changed values x 4 B"},
         "solve_floor": {"bytes": floor, "achieved_GBs": floor / (ms / 1e3) / 1e9,
                         "frac": floor / (ms / 1e3) / 1e9 / HBM_PEAK_GBS,
                         "rule": "28 B per node: 3 evaluations x 8 B + one 4 B write"},
