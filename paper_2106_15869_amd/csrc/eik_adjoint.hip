@@ -217,6 +217,20 @@ __global__ __launch_bounds__(kBlock) void k_adj_final(int n, const T* __restrict
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) out[i] = D[i] * lam[i];
 }
 
+// Whether a recomputed lambda differs from the one it replaces: by its bits, so
+// that a NaN (from dL/dphi, or from inf - inf in a sum) recomputed from the
+// same values is no change.  A changed chunk is evaluated again, so a NaN that
+// differed from itself would keep its tile listed for ever.  The system is
+// acyclic and a sum of the same values has the same bits, so the iteration
+// ends as it does for numbers.  (One instruction, like the comparison of the
+// values; testing for two NaNs beside it cost 4 % of a 192^3 training step.)
+__device__ __forceinline__ bool lambda_changed(float now, float was) {
+    return __float_as_uint(now) != __float_as_uint(was);
+}
+__device__ __forceinline__ bool lambda_changed(double now, double was) {
+    return __double_as_longlong(now) != __double_as_longlong(was);
+}
+
 // Resident workgroups per CU: six for 8^3 float tiles, so that all 1536
 // default workgroups of a launch are resident at once.  Others unconstrained.
 template <int ND, int NPT, typename T>
@@ -373,7 +387,7 @@ __global__ __launch_bounds__(kBlock, (adj_blocks_per_cu<ND, Shape<ND, TX, TY, TZ
                 T v = gv[r];
 #pragma unroll
                 for (int d = 0; d < 2 * ND; ++d) v = v + c[r][d] * (c[r][d] != T(0) ? l[r][d] : T(0));
-                const bool diff = ok[r] && v != cur[r];
+                const bool diff = ok[r] && lambda_changed(v, cur[r]);
                 cur[r] = diff ? v : cur[r];
                 slam[L0 + r * RSTEP] = cur[r];  // (only this lane writes it)
                 if (ballot64(diff)) changed |= bit;
@@ -387,7 +401,7 @@ __global__ __launch_bounds__(kBlock, (adj_blocks_per_cu<ND, Shape<ND, TX, TY, TZ
         uint32_t kmin = kNoKey;
 #pragma unroll
         for (int r = 0; r < S::NPT; ++r) {
-            if (!(cur[r] != old[r])) continue;
+            if (!lambda_changed(cur[r], old[r])) continue;
             a.lam[G[r]] = cur[r];
             const int f = static_cast<int>(u[r]) & E[r];
             if (f) {
