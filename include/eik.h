@@ -143,7 +143,9 @@ typedef struct {
                                   (8^3 in 3D, 16 x 16 in 2D) */
     int32_t inner_iters;       /* tile variant: inner iterations per tile visit; 0 = default:
                                   4 x the sum of the tile sides */
-    int64_t max_iters;         /* cap per loop (0 = default 4 * N + 64) */
+    int64_t max_iters;         /* cap per loop, in launches (0 = default 4 * N + 64).  Tile variant,
+                                  synchronous: the correcting update step may take twice as many,
+                                  and the remedy loop takes up what it leaves over */
     uint32_t flags;            /* EIK_FLAG_* */
     const double* source_values; /* host, n_sources entries; NULL -> all 0 */
     void* workspace;           /* device scratch of workspace_bytes; NULL -> the

@@ -1030,6 +1030,14 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
     TileOps<T> ku = k;
     if (two && !select_ops<T>(b.nd, cu, false, ku)) return fail(EIK_ERR_INVALID_ARGUMENT, "unsupported tile shape");
     const int64_t cap = o.max_iters > 0 ? o.max_iters : 4 * b.n + 64;
+    // Launches the correcting update step may take.  It does the work of the
+    // update step alone and of the remedy loop, cap launches each, on tiles half
+    // as wide in 2D: up to three times the longer of the two (a 4 x 19 grid: 3
+    // against 1 and 1; of 1500 random small grids two took more than twice as
+    // many; 2D lognormal 1024^2 130 against 64 and 127).  What it leaves over goes to
+    // the remedy loop with its cap launches.  An asynchronous call runs every
+    // launch of its budget, so there it is cap for each loop.
+    const int64_t cap2 = alone || async || cap > INT64_MAX / 2 ? cap : 2 * cap;
     // Inner iterations per tile visit: visits run until their lists empty
     // (4 x the sum of the sides is a safety cap), except in the 2D update step
     // alone, whose visits stop after the iterations a front needs to cross the
@@ -1172,11 +1180,11 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
     // solution takes 36 in all (45.5 -> 28.3 ms; 256^3 maze 13.2 -> 9.1 ms,
     // layered 192^3 5.4 -> 3.3 ms).
     int64_t n2 = 0;
-    auto loop = [&](auto step, int64_t first, int64_t* steps, bool report) {
+    auto loop = [&](auto step, int64_t first, int64_t most, int64_t* steps, bool report) {
         auto cnt = [&](int64_t t) { return counts(first + t); };
         if (async || pageable)
-            return run_loop(step, cnt, kSub * kPad, cap, async, s, steps, w.ctl, pageable, report);
-        return run_tile_loop(step, cnt, kSub * kPad, first, cap, s, steps);
+            return run_loop(step, cnt, kSub * kPad, most, async, s, steps, w.ctl, pageable, report);
+        return run_tile_loop(step, cnt, kSub * kPad, first, most, s, steps);
     };
     eik_status rc = loop(
         [&](int64_t t) {
@@ -1184,15 +1192,19 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
             return timed(prof, EIK_KERNEL_UPDATE,
                          [&] { return ku.update(iter_args(t, 0), geom_u, eT, inner_upd, gt, s); });
         },
-        0, &n2, alone);
+        0, cap2, &n2, alone);
     launched += n2;
+    if (rc == EIK_ERR_NO_CONVERGENCE && !alone) {  // the remedy loop takes up what is listed
+        g_last_error.clear();
+        rc = EIK_OK;
+    }
     Results res;
     bool have = false;  // res holds the call's results
     if (rc == EIK_OK && !skip_remedy) {
-        // STEP 3: detection adds to the list the next launch drains (what an
-        // asynchronous update step left over is still in it), then the remedy
-        // loop.  A synchronous call reads the list's length first, with its
-        // results: after the correcting update step it is empty.
+        // STEP 3: detection adds to the list the next launch drains (what the
+        // update step left over is still in it), then the remedy loop.  A
+        // synchronous call reads the list's length first, with its results: unless
+        // the correcting update step ran out of launches it is empty.
         HIP_TRY(detect(n2));
         launched += 1;
         int64_t n3 = 0;
@@ -1202,7 +1214,7 @@ eik_status solve_tile(const Batch& b, const T* F, double eps, T* phi, const eik_
             have = res.open == 0;
         }
         if (!have) {
-            rc = loop([&](int64_t t) { return visits(n2 + t, 1, t == 0); }, n2, &n3, true);
+            rc = loop([&](int64_t t) { return visits(n2 + t, 1, t == 0); }, n2, cap, &n3, true);
             launched += n3;
         }
     }
