@@ -199,12 +199,16 @@ __device__ __forceinline__ T eval_lds(const T* sphi, int L, T v, const Inst<T>& 
 // ---------------------------------------------------------------------------
 // A remedy visit
 // ---------------------------------------------------------------------------
+// Beside the dirty faces in a visit's mask word: a node of the tile takes the
+// general local solve.
+constexpr uint32_t kGeneral = 128u;
+
 // LDS of a remedy visit.
 template <typename T, typename Mask>
 struct RemedyLds {
     T* sphi;           // values with the one-cell halo
     Mask* act;         // [2][waves]: each wave's chunks that changed in an iteration (by parity)
-    uint32_t* mask;    // dirty faces the visit starts from
+    uint32_t* mask;    // dirty faces the visit starts from, kGeneral (0 between visits)
     int* face;         // faces a drop crossed
     int* evals;        // local-solver evaluations
     uint32_t* kmin;    // ordered: key of the smallest value that crossed a face (the caller sets kNoKey)
@@ -248,43 +252,48 @@ __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T
 #pragma unroll
     for (int r = 0; r < S::NPT; ++r) hv[r] = cells[static_cast<size_t>(t) * S::NT + threadIdx.x + r * kBlock];
     stage<T, ND, TX, TY, TZ, false, false>(g, x0, y0, z0, phi, nullptr, sphi, nullptr);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool lane0 = (threadIdx.x & 63) == 0;
+    T cur[S::NPT], old[S::NPT], hh[S::NPT];
+    constexpr bool AN2 = AN && ND == 2;
+    AnisoNode<T> an[AN2 ? S::NPT : 1];
+    bool fr[S::NPT], ends = false;
+#pragma unroll
+    for (int r = 0; r < S::NPT; ++r) {
+        fr[r] = cell_free<T, AN>(hv[r]);
+        if (!fr[r]) hv[r] = dead_value<T, AN>();  // never solves to a drop
+        hh[r] = hv[r] * hv[r];
+        if constexpr (AN2) {
+            an[r].set(g.d[0], g.d[1], hv[r]);
+            ends |= fr[r] && !an[r].fits();
+        } else {
+            ends |= fr[r] && !mid_range(hv[r]);
+        }
+    }
+    if (ends) atomicOr(s.mask, kGeneral);
     if (threadIdx.x == 0) {
         *s.face = 0;
         *s.evals = 0;
         *s.written = 0;
         *s.unreached = 0;
-        *s.mask = mask_in;
+        atomicOr(s.mask, mask_in);
     }
     __syncthreads();
     const uint32_t m = *s.mask;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool lane0 = (threadIdx.x & 63) == 0;
     int nx, ny, nz, L0;
     node_loc<ND, TX, TY, TZ>(threadIdx.x, nx, ny, nz, L0);
-    T cur[S::NPT], old[S::NPT], hh[S::NPT];
-    constexpr bool AN2 = AN && ND == 2;
-    AnisoNode<T> an[AN2 ? S::NPT : 1];
     int nfree[S::NPT];
     Mask todo = 0;  // chunks to evaluate (the wave looks at its own)
-    bool unreached = false, ends = false;
+    bool unreached = false;
 #pragma unroll
     for (int r = 0; r < S::NPT; ++r) {
         int x, y, z, L;
         node_loc<ND, TX, TY, TZ>(threadIdx.x + r * kBlock, x, y, z, L);
         const int E = edge_bits<ND, TX, TY, TZ>(x, y, z) & open;
         cur[r] = old[r] = sphi[L0 + r * RSTEP];
-        const bool fr = cell_free<T, AN>(hv[r]);
-        if (!fr) hv[r] = dead_value<T, AN>();  // never solves to a drop
-        hh[r] = hv[r] * hv[r];
-        nfree[r] = __popcll(ballot64(fr));
-        unreached |= fr && !(cur[r] < inf);
-        if constexpr (AN2) {
-            an[r].set(g.d[0], g.d[1], hv[r]);
-            ends |= fr && !an[r].fits();
-        } else {
-            ends |= fr && !mid_range(hv[r]);
-        }
-        if (ballot64(fr && ((m & kAllFaces) || (E & static_cast<int>(m))))) todo |= Mask(1) << (r * WAVES + wave);
+        nfree[r] = __popcll(ballot64(fr[r]));
+        unreached |= fr[r] && !(cur[r] < inf);
+        if (ballot64(fr[r] && ((m & kAllFaces) || (E & static_cast<int>(m))))) todo |= Mask(1) << (r * WAVES + wave);
     }
     if (ballot64(unreached) && lane0) *s.unreached = 1;
     pending = false;
@@ -347,7 +356,7 @@ __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T
         }
     };
     if constexpr (AN && !AN2) iterate(std::false_type{});
-    else if (ballot64(ends) == 0) iterate(std::true_type{});
+    else if (!(first_lane(m) & kGeneral)) iterate(std::true_type{});  // (the workgroup's choice: each has its own barrier)
     else iterate(std::false_type{});
     // write back what changed; a changed value that lies below the neighbour
     // across an open face crosses it
@@ -376,6 +385,7 @@ __device__ __forceinline__ int remedy_visit(const T* cells, T* phi, const Inst<T
         if (evals) atomicAdd(s.evals, evals);
         if (written) atomicAdd(s.written, written);
     }
+    if (threadIdx.x == 0) *s.mask = 0u;
     __syncthreads();
     return it;
 }
@@ -691,6 +701,7 @@ __global__ __launch_bounds__(kBlock, (remedy_blocks_per_cu<Shape<ND, TX, TY, TZ>
     __shared__ uint32_t s_mask;
     __shared__ uint32_t s_key, s_kmin;
     __shared__ int s_unreached;
+    if (threadIdx.x == 0) s_mask = 0u;  // (before the barrier of list_open)
     const uint32_t ntag = launch_tag(a);
     const unsigned long long e0 = first_entry(a);
     const int n = list_open(a, s_len);
