@@ -22,6 +22,7 @@
 #include "eik_device.hpp"
 #include "eik_internal.hpp"
 #include "eik_seglist.hpp"
+#include "eik_walk.hpp"
 
 namespace eik {
 
@@ -757,12 +758,13 @@ __global__ __launch_bounds__(kBlock) void k_apply_local(GridDims gd, const T* __
     const int x = ND == 3 ? p % gd.nx : p;
     const int y = ND == 3 ? p / gd.nx : 0;
     const bool x0 = x > 0, x1 = x + 1 < gd.nx, y0 = y > 0, y1 = ND == 3 && y + 1 < gd.ny;
-    for (int o0 = blockIdx.y * steps; o0 < outer; o0 += gridDim.y * steps) {
-        const int end = min(o0 + steps, outer);
-        int i = o0 * plane + p;
-        T behind = o0 > 0 ? phi[i - plane] : inf;
+    const int64_t walks = walk_count(outer, steps);
+    for (int64_t k = blockIdx.y; k < walks; k += gridDim.y) {
+        const Walk w = walk_of(k, outer, steps);
+        int64_t i = w.begin * plane + p;
+        T behind = w.begin > 0 ? phi[i - plane] : inf;
         T here = phi[i];
-        for (int o = o0; o < end; ++o, i += plane) {
+        for (int64_t o = w.begin; o < w.end; ++o, i += plane) {
             const T ahead = o + 1 < outer ? phi[i + plane] : inf;
             const T f = F[i];
             T ax = x0 ? phi[i - 1] : inf;
@@ -986,11 +988,8 @@ template <typename T>
 hipError_t launch_apply_local(const GridDims& g, const T* F, const T* phi, const Spacing<T>& h, T* out,
                               hipStream_t s) {
     const int plane = g.nd == 3 ? g.nx * g.ny : g.nx, outer = g.nd == 3 ? g.nz : g.ny;
-    // Planes per walk: the two values at its ends are read by the next walk
-    // too, so long walks, but at least half a million lanes (four waves for
-    // each of the 1024 SIMDs twice over).
-    const int steps = std::max(1, std::min(16, g.n >> 19));
-    const dim3 grid((plane + kBlock - 1) / kBlock, std::min((outer + steps - 1) / steps, 65535));
+    const int steps = walk_steps(g.n);
+    const dim3 grid((plane + kBlock - 1) / kBlock, walk_blocks(outer, steps));
     if (g.nd == 2)
         hipLaunchKernelGGL((k_apply_local<T, 2>), grid, dim3(kBlock), 0, s, g, F, phi, h, out, steps);
     else
