@@ -42,6 +42,7 @@
 #include "eik_batch.hpp"
 #include "eik_sched.hpp"
 #include "eik_tile.hpp"
+#include "eik_walk.hpp"
 
 namespace eik {
 
@@ -214,7 +215,7 @@ __global__ void k_adj_mark_sources(BatchGeom<T> bg, SrcBatch<T> b, uint8_t* up, 
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_adj_final(int n, const T* __restrict__ D,
                                                       const T* __restrict__ lam, T* __restrict__ out) {
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) out[i] = D[i] * lam[i];
+    for (int64_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += flat_step(gridDim.x)) out[i] = D[i] * lam[i];
 }
 
 // Whether a recomputed lambda differs from the one it replaces: by its bits, so
@@ -479,7 +480,6 @@ eik_status adj_run(const Batch& b, const T* F, const T* phi, const T* g, T* out,
     AdjWs w = adj_layout(ws, b, sizeof(T));
     const int64_t cap = o.max_iters > 0 ? o.max_iters : 4 * b.n + 64;
     const int inner = o.inner_iters > 0 ? o.inner_iters : 4 * (TX + TY + TZ);
-    const int dense = static_cast<int>(std::min<int64_t>((b.n + kBlock - 1) / kBlock, 1 << 20));
     const int tiles = static_cast<int>(std::min<int64_t>(b.ntiles, 1 << 16));
     const size_t blk_bytes = 8 * static_cast<size_t>(kStatFields) * kMaxStatBlocks;
     int64_t launched = 0;
@@ -546,7 +546,7 @@ eik_status adj_run(const Batch& b, const T* F, const T* phi, const T* g, T* out,
                           : run_tile_loop(step, counts, kSub * kPad, 0, cap, s, &nl);
     launched += nl;
     HIP_TRY(timed(prof, EIK_KERNEL_OTHER, [&] {
-        hipLaunchKernelGGL(k_adj_final<T>, dim3(dense), dim3(kBlock), 0, s, static_cast<int>(b.n),
+        hipLaunchKernelGGL(k_adj_final<T>, dim3(flat_blocks(b.n)), dim3(kBlock), 0, s, static_cast<int>(b.n),
                            static_cast<const T*>(w.D), static_cast<const T*>(w.lam), out);
         return hipGetLastError();
     }));

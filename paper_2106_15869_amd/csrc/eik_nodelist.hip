@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kBlock) void k_init(const T* __restrict__ F, T* __r
                                                  uint32_t* __restrict__ stamp, int n, Ctl* ctl) {
     const T inf = pos_inf<T>();
     bool bad = false;
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
+    for (int64_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += flat_step(gridDim.x)) {
         T f = F[i];
         bad |= !(f >= T(0)) || !(f < inf);
         phi[i] = inf;
@@ -877,17 +877,12 @@ __global__ __launch_bounds__(kBlock) void k_sum_stats(unsigned long long* blk, i
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-static inline int dense_blocks(int n) {
-    long long b = (static_cast<long long>(n) + kBlock - 1) / kBlock;
-    if (b < 1) b = 1;
-    if (b > (1 << 20)) b = 1 << 20;
-    return static_cast<int>(b);
-}
+static_assert(kFlatBlock == kBlock, "flat passes run workgroups of kBlock lanes");
 
 template <typename T>
 hipError_t launch_init(const T* F, T* phi, uint8_t* lab, uint32_t* stamp, int n, Ctl* ctl,
                        hipStream_t s) {
-    hipLaunchKernelGGL(k_init<T>, dim3(dense_blocks(n)), dim3(kBlock), 0, s, F, phi, lab, stamp, n,
+    hipLaunchKernelGGL(k_init<T>, dim3(flat_blocks(n)), dim3(kBlock), 0, s, F, phi, lab, stamp, n,
                        ctl);
     return hipGetLastError();
 }

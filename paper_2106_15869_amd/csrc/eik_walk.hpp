@@ -1,4 +1,9 @@
-// How the dense local pass covers a grid: walks of `steps` planes along the
+// How dense kernels cover a grid.
+//
+// Flat passes: node i and then every flat_step(blocks)-th one, in 64 bits: the
+// step past the last of nearly 2^31 nodes comes out negative in 32.
+//
+// The local pass: walks of `steps` planes along the
 // outer axis, walk k starting at plane k * steps.  Plane numbers are 64-bit: an
 // outer extent may lie just below 2^31, where a 32-bit step past the last walk
 // comes out negative.  (constexpr: host and device.)
@@ -7,6 +12,14 @@
 #include <stdint.h>
 
 namespace eik {
+
+constexpr int kFlatBlock = 256;  // lanes per workgroup
+
+constexpr int flat_blocks(int64_t n) {
+    const int64_t b = (n + kFlatBlock - 1) / kFlatBlock;
+    return b < 1 ? 1 : b < (1 << 20) ? static_cast<int>(b) : 1 << 20;
+}
+constexpr int64_t flat_step(int64_t blocks) { return blocks * kFlatBlock; }
 
 struct Walk {
     int64_t begin, end;  // planes

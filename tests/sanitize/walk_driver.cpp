@@ -1,5 +1,5 @@
-// The dense local pass's walks cover every plane once and stay in the grid,
-// also where the outer extent lies just below 2^31.
+// Flat passes cover every node once and the dense local pass's walks every plane
+// once, and both stay in the grid, also where it has nearly 2^31 nodes.
 #include <cstdio>
 #include <initializer_list>
 
@@ -29,12 +29,29 @@ static void covers(int64_t plane, int64_t outer) {
     }
 }
 
+static void flat(int64_t n) {
+    const int64_t lanes = flat_step(flat_blocks(n));
+    int64_t nodes = 0;
+    bool in = true;
+    // a lane's nodes are its number and what follows at the step; the lanes
+    // differ only in how many there are
+    for (int64_t lane : {int64_t(0), (n - 1) % lanes, lanes - 1}) {
+        int64_t c = 0;
+        for (int64_t i = lane; i < n; i += lanes) in &= i >= 0 && ++c > 0;
+        in &= c == (lane < n ? (n - 1 - lane) / lanes + 1 : 0);
+        nodes += c;
+    }
+    if (!in || nodes == 0) std::printf("flat %lld\n", (long long)n), ++fails;
+}
+
 int main() {
     const int64_t top = (int64_t(1) << 31) - 1;
     for (int64_t outer : {top, top - 1, top - 15, top - 16, top - 65535 * 16, top - 65535 * 16 - 1, top / 2})
         covers(1, outer);
     for (int64_t plane : {1, 2, 16, 33, 255, 257, 4096})
         for (int64_t outer : {1, 2, 15, 16, 17, 1000, 65535, 65536, 65537}) covers(plane, outer);
+    for (int64_t n : {int64_t(1), int64_t(255), int64_t(257), int64_t(1) << 28, (int64_t(1) << 28) + 1, top, top - 300})
+        flat(n);
     covers(2, top / 2);
     covers(top, 1);
     std::printf(fails ? "failed\n" : "clean\n");
