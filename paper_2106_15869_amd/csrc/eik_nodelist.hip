@@ -743,54 +743,54 @@ __global__ __launch_bounds__(kRunBlock) void k_node_run(NodeIter<T> a, GridDims 
 // One dense pass: a lane owns an index of a plane (a row in 2D) and walks
 // `steps` planes along the outer axis, keeping the values behind and ahead in
 // registers, so that a node costs one new value and one speed from memory (the
-// neighbours in the plane are L1 hits) and no division of its index.  Any
-// extents keep all lanes busy but those past the end of the last block.
-// 200 x 333 x 250 float, a whole call: 82 us, 123 us with an index decoded and
+// neighbours in the plane are L1 hits) and no division of its index.  Lanes are
+// numbered through the planes of all walks (eik_walk.hpp), so narrow ones keep
+// them busy too: blocks within one plane took 174 us for 1 M x 16 float, where an
+// index decoded per node took 80.
+// 200 x 333 x 250 float, a whole call: 75 us, 108 us with an index decoded and
 // seven values loaded per node and the general solve (200 MB: 40 us at 5 TB/s).
 template <typename T, int ND>
 __global__ __launch_bounds__(kBlock) void k_apply_local(GridDims gd, const T* __restrict__ F,
                                                         const T* __restrict__ phi, Spacing<T> sp,
                                                         T* __restrict__ out, int steps) {
     const T inf = pos_inf<T>();
-    const int plane = ND == 3 ? gd.nx * gd.ny : gd.nx, outer = ND == 3 ? gd.nz : gd.ny;
-    const int p = blockIdx.x * kBlock + threadIdx.x;
-    if (p >= plane) return;
-    const int x = ND == 3 ? p % gd.nx : p;
-    const int y = ND == 3 ? p / gd.nx : 0;
-    const bool x0 = x > 0, x1 = x + 1 < gd.nx, y0 = y > 0, y1 = ND == 3 && y + 1 < gd.ny;
-    const int64_t walks = walk_count(outer, steps);
-    for (int64_t k = blockIdx.y; k < walks; k += gridDim.y) {
-        const Walk w = walk_of(k, outer, steps);
-        int64_t i = w.begin * plane + p;
-        T behind = w.begin > 0 ? phi[i - plane] : inf;
-        T here = phi[i];
-        for (int64_t o = w.begin; o < w.end; ++o, i += plane) {
-            const T ahead = o + 1 < outer ? phi[i + plane] : inf;
-            const T f = F[i];
-            T ax = x0 ? phi[i - 1] : inf;
-            if (x1) ax = tmin(ax, phi[i + 1]);
-            T ay = inf;
-            if (ND == 3) {
-                if (y0) ay = phi[i - gd.nx];
-                if (y1) ay = tmin(ay, phi[i + gd.nx]);
-            }
-            const T ao = tmin(behind, ahead);
-            T v;
-            if (sp.aniso) {
-                v = ND == 2 ? local_solve<T, 2>(ao, ax, inf, f, sp) : local_solve<T, 3>(ao, ay, ax, f, sp);
-            } else {
-                const T H = cell_H(sp.h, f);
-                if (__builtin_amdgcn_ballot_w64(H < inf && !mid_range(H)) == 0) {
-                    v = ND == 2 ? godunov_mid<T, 2>(ao, ax, inf, H, H * H) : godunov_mid<T, 3>(ao, ay, ax, H, H * H);
-                    if (!(H < inf) || !(tmin(tmin(ao, ax), ay) < inf)) v = inf;
-                } else {
-                    v = ND == 2 ? godunov<T, 2>(ao, ax, inf, H) : godunov<T, 3>(ao, ay, ax, H);
-                }
-            }
-            out[i] = v;
-            behind = here;
-            here = ahead;
+    const uint32_t plane = ND == 3 ? gd.nx * gd.ny : gd.nx, outer = ND == 3 ? gd.nz : gd.ny;
+    const uint32_t lane = blockIdx.x * kBlock + threadIdx.x;
+    if (lane >= walk_lanes(plane, outer, steps)) return;
+    const uint32_t nx = gd.nx, ny = gd.ny, p = lane % plane;
+    const uint32_t x = ND == 3 ? p % nx : p, y = ND == 3 ? p / nx : 0;
+    const bool x0 = x > 0, x1 = x + 1 < nx, y0 = y > 0, y1 = ND == 3 && y + 1 < ny;
+    const Walk w = walk_of(lane / plane, outer, steps);
+    const int step = static_cast<int>(plane);
+    int i = static_cast<int>(w.begin * plane + p);
+    T behind = w.begin > 0 ? phi[i - step] : inf;
+    T here = phi[i];
+    for (uint32_t o = w.begin; o < w.end; ++o, i = static_cast<int>(i + plane)) {
+        const T ahead = o + 1 < outer ? phi[i + step] : inf;
+        const T f = F[i];
+        T ax = x0 ? phi[i - 1] : inf;
+        if (x1) ax = tmin(ax, phi[i + 1]);
+        T ay = inf;
+        if (ND == 3) {
+            if (y0) ay = phi[i - gd.nx];
+            if (y1) ay = tmin(ay, phi[i + gd.nx]);
         }
+        const T ao = tmin(behind, ahead);
+        T v;
+        if (sp.aniso) {
+            v = ND == 2 ? local_solve<T, 2>(ao, ax, inf, f, sp) : local_solve<T, 3>(ao, ay, ax, f, sp);
+        } else {
+            const T H = cell_H(sp.h, f);
+            if (__builtin_amdgcn_ballot_w64(H < inf && !mid_range(H)) == 0) {
+                v = ND == 2 ? godunov_mid<T, 2>(ao, ax, inf, H, H * H) : godunov_mid<T, 3>(ao, ay, ax, H, H * H);
+                if (!(H < inf) || !(tmin(tmin(ao, ax), ay) < inf)) v = inf;
+            } else {
+                v = ND == 2 ? godunov<T, 2>(ao, ax, inf, H) : godunov<T, 3>(ao, ay, ax, H);
+            }
+        }
+        out[i] = v;
+        behind = here;
+        here = ahead;
     }
 }
 
@@ -983,8 +983,8 @@ template <typename T>
 hipError_t launch_apply_local(const GridDims& g, const T* F, const T* phi, const Spacing<T>& h, T* out,
                               hipStream_t s) {
     const int plane = g.nd == 3 ? g.nx * g.ny : g.nx, outer = g.nd == 3 ? g.nz : g.ny;
-    const int steps = walk_steps(g.n);
-    const dim3 grid((plane + kBlock - 1) / kBlock, walk_blocks(outer, steps));
+    const int steps = walk_steps(g.n, plane);
+    const dim3 grid(static_cast<uint32_t>((walk_lanes(plane, outer, steps) + kBlock - 1) / kBlock));
     if (g.nd == 2)
         hipLaunchKernelGGL((k_apply_local<T, 2>), grid, dim3(kBlock), 0, s, g, F, phi, h, out, steps);
     else

@@ -3,10 +3,10 @@
 // Flat passes: node i and then every flat_step(blocks)-th one, in 64 bits: the
 // step past the last of nearly 2^31 nodes comes out negative in 32.
 //
-// The local pass: walks of `steps` planes along the
-// outer axis, walk k starting at plane k * steps.  Plane numbers are 64-bit: an
-// outer extent may lie just below 2^31, where a 32-bit step past the last walk
-// comes out negative.  (constexpr: host and device.)
+// The local pass: walks of `steps` planes along the outer axis, walk k starting
+// at plane k * steps; lane l takes node l % plane of walk l / plane.  Plane
+// numbers are unsigned: the end of a walk may lie past 2^31.  (constexpr: host
+// and device.)
 #pragma once
 
 #include <stdint.h>
@@ -22,28 +22,31 @@ constexpr int flat_blocks(int64_t n) {
 constexpr int64_t flat_step(int64_t blocks) { return blocks * kFlatBlock; }
 
 struct Walk {
-    int64_t begin, end;  // planes
+    uint32_t begin, end;  // planes
 };
 
 constexpr int64_t walk_count(int64_t outer, int steps) { return (outer + steps - 1) / steps; }
 
-constexpr Walk walk_of(int64_t k, int64_t outer, int steps) {
-    const int64_t begin = k * steps, end = begin + steps;
+constexpr Walk walk_of(uint32_t k, uint32_t outer, int steps) {
+    const uint32_t begin = k * static_cast<uint32_t>(steps), end = begin + static_cast<uint32_t>(steps);
     return Walk{begin, end < outer ? end : outer};
 }
 
 // Planes per walk: the two values at its ends are read by the next walk too, so
 // long walks, but at least half a million lanes (four waves for each of the
-// 1024 SIMDs twice over).
-constexpr int walk_steps(int64_t n) {
-    const int64_t s = n >> 19;
-    return s < 1 ? 1 : s < 16 ? static_cast<int>(s) : 16;
+// 1024 SIMDs twice over), and no more than eight planes (16 M nodes: 257^3
+// float 100 us at 1, 89 at 2, 73 at 4 and 8, 78 at 16; 65280 x 257 double 125,
+// 100, 101, 105, 110).  With fewer than sixteen nodes a plane the lanes of a
+// wave read as many lines as they walk: two planes (16 M x 1 float 75 us at 1, 62
+// at 2, 136 at 8; 2 M x 8 double 109 at 1 and 2, 121 at 8).
+constexpr int walk_steps(int64_t n, int64_t plane) {
+    const int64_t s = n >> 19, most = plane < 16 ? 2 : 8;
+    return s < 1 ? 1 : static_cast<int>(s < most ? s : most);
 }
 
-// Blocks along the walks (grid.y), each of which takes every such walk.
-constexpr int walk_blocks(int64_t outer, int steps) {
-    const int64_t k = walk_count(outer, steps);
-    return k < 65535 ? static_cast<int>(k) : 65535;
-}
+// A lane per node of a plane and walk, numbered through: the lanes of a wave may
+// lie in different walks, so planes of any size fill it.  No more than the
+// grid has nodes (31 bits).
+constexpr int64_t walk_lanes(int64_t plane, int64_t outer, int steps) { return plane * walk_count(outer, steps); }
 
 }  // namespace eik

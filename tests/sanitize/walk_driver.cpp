@@ -10,19 +10,19 @@ using namespace eik;
 static int fails = 0;
 
 static void covers(int64_t plane, int64_t outer) {
-    const int steps = walk_steps(plane * outer);
+    const int steps = walk_steps(plane * outer, plane);
     const int64_t walks = walk_count(outer, steps);
-    const int blocks = walk_blocks(outer, steps);
-    int64_t planes = 0, taken = 0;
-    bool in = true;
-    for (int64_t b = 0; b < blocks; ++b)
-        for (int64_t k = b; k < walks; k += blocks) {
-            const Walk w = walk_of(k, outer, steps);
-            in &= w.begin >= 0 && w.begin < w.end && w.end <= outer && w.begin == k * steps;
-            planes += w.end - w.begin;
-            ++taken;
-        }
-    if (!in || planes != outer || taken != walks) {
+    int64_t planes = 0;
+    bool in = walk_lanes(plane, outer, steps) <= plane * outer;
+    for (int64_t k = 0; k < walks; ++k) {
+        const Walk w = walk_of(static_cast<uint32_t>(k), static_cast<uint32_t>(outer), steps);
+        in &= w.begin == planes && w.begin < w.end && w.end <= outer;
+        planes += w.end - w.begin;
+    }
+    // the last lane is the last node of the last walk
+    const int64_t last = walk_lanes(plane, outer, steps) - 1;
+    in &= last / plane == walks - 1 && last % plane == plane - 1;
+    if (!in || planes != outer) {
         std::printf("plane %lld outer %lld: in %d planes %lld\n", (long long)plane, (long long)outer, in,
                     (long long)planes);
         ++fails;
@@ -46,7 +46,7 @@ static void flat(int64_t n) {
 
 int main() {
     const int64_t top = (int64_t(1) << 31) - 1;
-    for (int64_t outer : {top, top - 1, top - 15, top - 16, top - 65535 * 16, top - 65535 * 16 - 1, top / 2})
+    for (int64_t outer : {top, top - 1})
         covers(1, outer);
     for (int64_t plane : {1, 2, 16, 33, 255, 257, 4096})
         for (int64_t outer : {1, 2, 15, 16, 17, 1000, 65535, 65536, 65537}) covers(plane, outer);
