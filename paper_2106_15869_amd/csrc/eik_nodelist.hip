@@ -781,9 +781,12 @@ __global__ __launch_bounds__(kBlock) void k_apply_local(GridDims gd, const T* __
             v = ND == 2 ? local_solve<T, 2>(ao, ax, inf, f, sp) : local_solve<T, 3>(ao, ay, ax, f, sp);
         } else {
             const T H = cell_H(sp.h, f);
-            if (__builtin_amdgcn_ballot_w64(H < inf && !mid_range(H)) == 0) {
+            // (a NaN among the minima is for the general solve: what it makes of one
+            // depends on the order of its comparisons)
+            const bool nan = __builtin_isunordered(ao, ax) || __builtin_isunordered(ay, ay);
+            if (__builtin_amdgcn_ballot_w64(H < inf && (nan || !mid_range(H))) == 0) {
                 v = ND == 2 ? godunov_mid<T, 2>(ao, ax, inf, H, H * H) : godunov_mid<T, 3>(ao, ay, ax, H, H * H);
-                if (!(H < inf) || !(tmin(tmin(ao, ax), ay) < inf)) v = inf;
+                if (!(H < inf) || !(vmin(vmin(ao, ax), ay) < inf)) v = inf;
             } else {
                 v = ND == 2 ? godunov<T, 2>(ao, ax, inf, H) : godunov<T, 3>(ao, ay, ax, H);
             }
