@@ -61,6 +61,29 @@ struct AdjIter : Sched {
     const T* pull;      // pulled weights, tile-major: [tile][direction][node]
 };
 
+// A tile's nodes in the tile-major arrays: the nodes of the grid, tile after
+// tile, x fastest within one.  A tile at the grid's end is cut there, so the
+// arrays have an entry per node: with whole tiles a 1 x 4096 x 4096 grid had
+// eight (3.2 GB of weights in place of 400 MB).
+struct TileBlock {
+    int first;       // entry of the tile's first node
+    int bx, by, bz;  // its extents
+    __device__ __forceinline__ int nodes() const { return bx * by * bz; }
+    // in-tile position of a node, clamped into the tile
+    __device__ __forceinline__ int at(int x, int y, int z) const {
+        return (min(z, bz - 1) * by + min(y, by - 1)) * bx + min(x, bx - 1);
+    }
+};
+template <int ND, int TX, int TY, int TZ, typename T>
+__device__ __forceinline__ TileBlock tile_block(const Inst<T>& g, int x0, int y0, int z0) {
+    TileBlock b;
+    b.bx = min(TX, g.nx - x0);
+    b.by = min(TY, g.ny - y0);
+    b.bz = ND == 3 ? min(TZ, g.nz - z0) : 1;
+    b.first = g.node_base + (z0 * g.ny + b.bz * y0) * g.nx + b.bz * b.by * x0;
+    return b;
+}
+
 // ---------------------------------------------------------------------------
 // One workgroup per tile: phi with a halo of two nodes in LDS, from it the
 // stencil of the tile's nodes and of a halo of one, from that the weights each
@@ -156,19 +179,21 @@ __global__ __launch_bounds__(kBlock) void k_adj_prep(AdjIter<T> a, BatchGeom<T> 
         }
         __syncthreads();
         bool nz = false;
+        const TileBlock tb = tile_block<ND, TX, TY, TZ>(I, x0, y0, z0);
+        T* const tile_pull = pull + static_cast<size_t>(tb.first) * (2 * ND);
         for (int n = threadIdx.x; n < S::NT; n += kBlock) {
             int x, y, z, L;
             node_loc<ND, TX, TY, TZ>(n, x, y, z, L);
-            const size_t e = static_cast<size_t>(t) * S::NT;
-            up[e + n] = sup[L];
+            if (!inside(x0 + x, y0 + y, z0 + z)) continue;
+            const int q = tb.at(x, y, z);
+            up[tb.first + q] = sup[L];
 #pragma unroll
             for (int d = 0; d < 2 * ND; ++d) {
                 // the neighbour in direction d pushes to this node if its upwind
                 // neighbour on that axis lies in the opposite direction
                 const int p = L + lds_offset<ND, TX, TY, TZ>(d);
-                pull[e * (2 * ND) + d * S::NT + n] = (sup[p] >> (d ^ 1)) & 1u ? sw[d >> 1][p] : T(0);
+                tile_pull[d * tb.nodes() + q] = (sup[p] >> (d ^ 1)) & 1u ? sw[d >> 1][p] : T(0);
             }
-            if (!inside(x0 + x, y0 + y, z0 + z)) continue;
             const int i = node(x0 + x, y0 + y, z0 + z);
             a.lam[i] = T(0);
             if (a.g[i] != T(0)) {
@@ -187,28 +212,25 @@ __global__ __launch_bounds__(kBlock) void k_adj_prep(AdjIter<T> a, BatchGeom<T> 
 // A source has no stencil: nothing pulls from it, and it has no gradient.
 template <typename T, int ND, int TX, int TY, int TZ>
 __global__ void k_adj_mark_sources(BatchGeom<T> bg, SrcBatch<T> b, uint8_t* up, T* pull, T* D) {
-    using S = Shape<ND, TX, TY, TZ>;
     const int k = threadIdx.x;
     if (k >= b.count) return;
     const Inst<T> g = bg.ninst == 1 ? bg.one : bg.table[b.inst[k]];
     const int i = b.idx[k] - g.node_base;
     const int x = i % g.nx, y = (i / g.nx) % g.ny, z = i / (g.nx * g.ny);
     D[b.idx[k]] = T(0);
-    auto entry = [&](int X, int Y, int Z, size_t& e, int& n) {
-        const int t = g.tile_base + ((Z / (ND == 3 ? TZ : 1)) * g.nty + Y / TY) * g.ntx + X / TX;
-        e = static_cast<size_t>(t) * S::NT;
-        n = ((ND == 3 ? Z % TZ : 0) * TY + Y % TY) * TX + X % TX;
+    auto block = [&](int X, int Y, int Z) {
+        return tile_block<ND, TX, TY, TZ>(g, X / TX * TX, Y / TY * TY, ND == 3 ? Z / TZ * TZ : 0);
     };
-    size_t e;
-    int n;
-    entry(x, y, z, e, n);
-    up[e + n] = 0;
+    auto pos = [&](const TileBlock& tb, int X, int Y, int Z) { return tb.at(X % TX, Y % TY, ND == 3 ? Z % TZ : 0); };
+    const TileBlock own = block(x, y, z);
+    up[own.first + pos(own, x, y, z)] = 0;
     constexpr int dx[6] = {-1, 1, 0, 0, 0, 0}, dy[6] = {0, 0, -1, 1, 0, 0}, dz[6] = {0, 0, 0, 0, -1, 1};
     for (int d = 0; d < 2 * ND; ++d) {
         const int X = x + dx[d], Y = y + dy[d], Z = z + dz[d];
         if (X < 0 || X >= g.nx || Y < 0 || Y >= g.ny || Z < 0 || Z >= g.nz) continue;
-        entry(X, Y, Z, e, n);
-        pull[e * (2 * ND) + (d ^ 1) * S::NT + n] = T(0);  // seen from there the source lies the other way
+        const TileBlock tb = block(X, Y, Z);
+        // seen from there the source lies the other way
+        pull[static_cast<size_t>(tb.first) * (2 * ND) + (d ^ 1) * tb.nodes() + pos(tb, X, Y, Z)] = T(0);
     }
 }
 
@@ -319,21 +341,22 @@ __global__ __launch_bounds__(kBlock, (adj_blocks_per_cu<ND, Shape<ND, TX, TY, TZ
                 const int cz = min(max(gz, 0), g.nz - 1);
                 vl[j] = a.lam[g.node_base + (cz * g.ny + cy) * g.nx + cx];
             }
-            const size_t e = static_cast<size_t>(t) * S::NT;
+            const TileBlock tb = tile_block<ND, TX, TY, TZ>(g, x0, y0, z0);
+            const T* const tile_pull = a.pull + static_cast<size_t>(tb.first) * (2 * ND);
 #pragma unroll
             for (int r = 0; r < S::NPT; ++r) {
-                const int nn = threadIdx.x + r * kBlock;
                 int x, y, z, L;
-                node_loc<ND, TX, TY, TZ>(nn, x, y, z, L);
+                node_loc<ND, TX, TY, TZ>(threadIdx.x + r * kBlock, x, y, z, L);
+                const int q = tb.at(x, y, z);
                 ok[r] = x0 + x < g.nx && y0 + y < g.ny && z0 + z < g.nz;
                 E[r] = edge_bits<ND, TX, TY, TZ>(x, y, z) & open;
                 G[r] = g.node_base + (min(z0 + z, g.nz - 1) * g.ny + min(y0 + y, g.ny - 1)) * g.nx + min(x0 + x, g.nx - 1);
                 gv[r] = a.g[G[r]];
-                u[r] = a.up[e + nn];
+                u[r] = a.up[tb.first + q];
                 ph[r] = T(0);
                 if (E[r]) ph[r] = a.phi[G[r]];
 #pragma unroll
-                for (int d = 0; d < 2 * ND; ++d) c[r][d] = a.pull[e * (2 * ND) + d * S::NT + nn];
+                for (int d = 0; d < 2 * ND; ++d) c[r][d] = tile_pull[d * tb.nodes() + q];
             }
 #pragma unroll
             for (int j = 0; j < NIT; ++j) {
@@ -458,9 +481,8 @@ AdjWs adj_layout(char* base, const Batch& b, size_t esz) {
     const size_t n = static_cast<size_t>(b.n);
     w.ctl = reinterpret_cast<Ctl*>(take(sizeof(Ctl)));
     w.blkstat = reinterpret_cast<unsigned long long*>(take(8 * static_cast<size_t>(kStatFields) * kMaxStatBlocks));
-    const size_t entries = static_cast<size_t>(b.ntiles) * b.cfg.tx * b.cfg.ty * b.cfg.tz;  // tile-major
-    w.up = reinterpret_cast<uint8_t*>(take(entries));
-    w.pull = take(2 * static_cast<size_t>(b.nd) * esz * entries);
+    w.up = reinterpret_cast<uint8_t*>(take(n));
+    w.pull = take(2 * static_cast<size_t>(b.nd) * esz * n);
     w.D = take(esz * n);
     w.lam = take(esz * n);
     w.q = sched_layout(take, b.ntiles);
