@@ -293,9 +293,9 @@ typedef struct {
  *                default shapes, the only ones it runs on), workspace (used
  *                when large enough, else the library allocates); out: tile,
  *                inner_iters, order_min and workgroups of the fastest
- *                candidate, variant = EIK_VARIANT_TILE (tile (0, 0, 0) when
- *                the default shapes won; 0 for a default order_min or
- *                workgroups)
+ *                candidate, variant = EIK_VARIANT_TILE (tile (0, 0, 0) only
+ *                with EIK_FLAG_SKIP_REMEDY in 2D; 0 for a default order_min
+ *                or workgroups)
  *   report       host, nullable: up to report_cap timed candidates;
  *                *n_report (nullable) receives the count written
  * The choice is cached per (ndim, dtype, log2 of N, per-axis spacing or

@@ -40,27 +40,19 @@ constexpr uint32_t kScheduleFlags = EIK_FLAG_SKIP_REMEDY | EIK_FLAG_FIFO_REMEDY;
 // Flags a cached choice belongs to.
 constexpr uint32_t kCacheFlags = kScheduleFlags | EIK_FLAG_NO_EARLY_REMEDY;
 
-// A zero tile is the library default: in 2D that runs the update step on
-// 32 x 32 tiles and detection/remedy on 16 x 16, a pairing no explicit shape
-// gives.  Per-axis spacing (Eq 5) is supported on the default shapes only
-// (16 x 16 in 2D, 8^3 in 3D), so only those are timed then; the zero tile is
-// then the same configuration as the explicit default and is left out.
-std::vector<Choice> candidates(int nd, bool aniso) {
+// The default shapes (16 x 16 in 2D, 8^3 in 3D) come explicitly.  A zero tile is
+// another configuration in the 2D update step alone only, which then runs on 32
+// x 32 tiles.  Per-axis spacing (Eq 5) is supported on the default shapes, so
+// only those are timed then.
+std::vector<Choice> candidates(int nd, bool aniso, uint32_t flags) {
     std::vector<Choice> all;
     if (nd == 2)
-        all = {{{0, 0, 0}, 0}, {{1, 16, 16}, 0}, {{1, 16, 16}, 48}, {{1, 32, 32}, 0},
-               {{1, 16, 64}, 0}, {{1, 8, 32}, 0}, {{1, 64, 64}, 0}};
+        all = {{{1, 16, 16}, 0}, {{1, 16, 16}, 48}, {{1, 32, 32}, 0}, {{1, 16, 64}, 0}, {{1, 8, 32}, 0}, {{1, 64, 64}, 0}};
     else
         all = {{{8, 8, 8}, 0}, {{8, 8, 8}, 16}, {{4, 8, 8}, 0}, {{4, 4, 16}, 0}, {{8, 8, 16}, 0}};
-    if (!aniso) return all;
-    std::vector<Choice> out;
-    for (const Choice& c : all) {
-        const bool zero = c.tile[0] == 0 && c.tile[1] == 0 && c.tile[2] == 0;
-        const bool def = nd == 2 ? (c.tile[1] == 16 && c.tile[2] == 16)
-                                 : (c.tile[0] == 8 && c.tile[1] == 8 && c.tile[2] == 8);
-        if (def && !zero) out.push_back(c);
-    }
-    return out;
+    if (aniso) all.resize(2);  // the default shape, with either cap
+    if (nd == 2 && !aniso && (flags & EIK_FLAG_SKIP_REMEDY)) all.insert(all.begin(), Choice{{0, 0, 0}, 0});
+    return all;
 }
 
 struct Events {
@@ -128,7 +120,7 @@ EIK_API eik_status eik_tune(const void* F, int32_t ndim, const int64_t* dims, do
     base.stats = nullptr;
     base.order_min = 0;
     base.workgroups = 0;
-    const std::vector<Choice> cand = candidates(ndim, aniso);
+    const std::vector<Choice> cand = candidates(ndim, aniso, base.flags);
     size_t need = 0;
     for (const Choice& c : cand) {
         eik_options q = base;
