@@ -13,7 +13,7 @@ the far face z = 255), the plain node-list schedule, the tile schedule with a
 first-in first-out remedy, the fast iterative method (FIM, the paper's
 baseline) on the same node lists, the dominant kernel's achieved bandwidth
 against the 8 TB/s HBM peak (device time from HIP events on the library's
-stream; bytes = 8 per local-solver evaluation + 4 per changed value, from the
+stream; bytes = 8 per node of a visited tile + 4 per changed value, from the
 solve's own counters), the whole solve against the 28 B/node floor, and the
 float64 fast-marching oracle on the host as a CPU baseline (median of 3 runs).
 

@@ -86,11 +86,10 @@ enum {
     EIK_FLAG_PROFILE = 8u,
     /* Tile variant: run the correcting update step and the remedy loop
        first-in first-out, every queued tile in every launch.  By default each
-       launch instead processes the
-       queued tiles whose pending values are lowest (about a thousand, chosen
-       by a sample of per-tile keys) and defers the others, so corrections
-       flow roughly in increasing value and fewer nodes are corrected twice.
-       Same rules and fixed point either way. */
+       launch instead processes the queued tiles whose pending values are
+       lowest (about a thousand, see order_min) and defers the others, so
+       corrections flow roughly in increasing value and fewer nodes are
+       corrected twice.  Same rules and fixed point either way. */
     EIK_FLAG_FIFO_REMEDY = 16u,
     /* 3D tile variant: run the update step alone, then detection and the
        remedy.  By default the update step's tile visits already apply the
@@ -158,10 +157,14 @@ typedef struct {
                                   all zero -> the isotropic h argument; else the
                                   first ndim entries must be finite and > 0 and
                                   replace h (which must still be valid) */
-    int32_t order_min;         /* tile variant, ordered remedy: a remedy launch
-                                  takes at least this many of the queued tiles
-                                  with the lowest keys; 0 = default (1024 in 3D,
-                                  512 in 2D) */
+    int32_t order_min;         /* tile variant, ordered visits: about how many of
+                                  the queued tiles, those with the lowest keys, a
+                                  launch takes; 0 = default (1024 in 3D, 512 in
+                                  2D).  A target: a launch aims at a quarter more,
+                                  and at an eighth of the queued tiles if that is
+                                  more, by a quantile of 64 sampled keys, and may
+                                  take fewer (at least one); with no more queued
+                                  than it aims at, it takes them all */
     int32_t workgroups;        /* tile variant: persistent workgroups per tile
                                   launch, a multiple of 8 up to 2048; 0 = default
                                   (1536 in 3D: six resident per CU on 256 CUs;
@@ -341,7 +344,7 @@ eik_status eik_async_status(const void* workspace, void* stream);
  *   (EIK_ERR_UNSUPPORTED): the call is synchronous.
  * Errors as eik_solve, and EIK_ERR_OUT_OF_MEMORY, before any device work,
  * when eik_workspace_size for the shape and options exceeds 128 MiB (e.g.
- * the tile variant takes 90 MiB at 256^3 and 98 MiB at 4096^2 in float32;
+ * the tile variant takes 82 MiB at 256^3 and 84 MiB at 4096^2 in float32;
  * the node-list variants need about 60 bytes per node and fit up to about
  * 2 M nodes).
  * Every call on one GPU shares that GPU's array, which keeps the last

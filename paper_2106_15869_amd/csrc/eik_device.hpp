@@ -48,8 +48,9 @@ __device__ __forceinline__ double vmax(double a, double b) {
     return r;
 }
 
-// Correctly rounded square root of x = 0, x >= 2^-96 or x = +inf.  The
-// instruction's result s is within one unit u in the last place of the root;
+// Correctly rounded square root of x = 0, x >= 2^-96 or x = +inf, by Tuckerman's
+// rounding test (Agarwal, Cooley, Gustavson, Shearer, Slishman, Tuckerman, IBM J.
+// Res. Dev. 30, 1986) on both sides.  The instruction's result s is within one unit u in the last place of the root;
 // as x is a float, the root lies beyond the midpoint of s and s + u exactly if
 // x > s (s + u), and before that of s - u and s if x <= s (s - u); both
 // residuals are signed exactly by a fused multiply-add.  (At 0 and +inf the
@@ -66,7 +67,9 @@ __device__ __forceinline__ float sqrt_mid(float x) {
 __device__ __forceinline__ double sqrt_mid(double x) { return dev_sqrt(x); }
 
 // x / 3, correctly rounded (finite x, no underflow): a quotient by the rounded
-// reciprocal, corrected by its exact remainder.
+// reciprocal, corrected by its exact remainder (Markstein, IBM J. Res. Dev. 34,
+// 1990; for a divisor known in advance, Brisebarre, Muller, Raina, IEEE Trans.
+// Comput. 53, 2004).
 __device__ __forceinline__ float third(float x) {
     const float c = 1.0f / 3.0f, q = x * c;
     return __builtin_fmaf(__builtin_fmaf(-3.0f, q, x), c, q);
@@ -231,10 +234,12 @@ __device__ __forceinline__ T godunov_aniso(T a0, T a1, T a2, T H0, T H1, T H2) {
 }
 
 // godunov_aniso in 2D with everything that depends on the node alone formed
-// once, the same value bit for bit: H_k, w_k, A = w_0 + w_1 (the sum does not
+// once, the same value bit for bit (where that one does not overflow: with a ratio
+// of spacings above 2^34 its discriminant may be inf - inf): H_k, w_k, A = w_0 + w_1 (the sum does not
 // depend on the order) and its rounded reciprocal, by which the last quotient is
-// formed and corrected by its exact remainder (correctly rounded unless A's
-// digits are all ones, which fits() excludes).  In the loop of a tile visit the
+// formed and corrected by its exact remainder as in third() (Markstein's
+// correction: correctly rounded unless A's digits are all ones, which fits()
+// excludes).  In the loop of a tile visit the
 // general form divides three to five times.
 template <typename T>
 struct AnisoNode {

@@ -55,14 +55,14 @@ inline int workgroups_of(int nd, int32_t opt, int64_t ntiles) {
     return most < w ? static_cast<int>(most) : w;
 }
 
-// Ordered scheduling: a launch takes at least this many of the queued tiles with
-// the lowest order keys.  A 2D front is a curve and keeps fewer tiles final at a
-// time than a 3D one.
+// Ordered scheduling: about how many of the queued tiles, those with the lowest
+// order keys, a launch takes (a target, see sampled_threshold).  A 2D front is a
+// curve and keeps fewer tiles final at a time than a 3D one.
 inline int order_min(int nd) { return nd == 2 ? 512 : 1024; }
-// The per-launch minimum a call uses (eik_options.order_min, 0: default).
+// The target a call uses (eik_options.order_min, 0: default).
 inline int order_min_of(int nd, int32_t opt) { return opt > 0 ? opt : order_min(nd); }
-// The threshold comes from a sample (sampled_threshold in eik_sched.hpp): a
-// launch aims at a quarter more, so that it rarely takes fewer.  Measured
+// The threshold comes from a sample (sampled_threshold in eik_sched.hpp), whose
+// count scatters: a launch aims at a quarter more, so that it mostly takes no fewer.  Measured
 // against the number aimed at, forward: 2D lognormal 4096^2 11.2 ms at 512, 11.5
 // at 768, 12.1 at 1024, 3000^2 with six sources 3.9, 3.6, 3.6; 3D maze 256^3
 // 4.75 ms at 1024, 4.5 at 1536, 4.55 at 2048, layered 3.0, 2.7, 2.7, lognormal

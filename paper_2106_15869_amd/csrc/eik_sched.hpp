@@ -197,17 +197,22 @@ __device__ __forceinline__ int list_open(const Sched& a, int* s_len) {
 }
 
 // Ordered: the largest key a launch takes, so that it visits about order_aim
-// of its n tiles (more than order_aim), or n / kListShare if that is more.  The quantile of 64 listed keys, spread over the
-// sub-lists: every workgroup draws the same sample (one 8-byte load per lane)
-// and ranks it without LDS.  The count is off by some 6 % of n, which costs
-// nothing.  At least one tile is taken: the one whose entry has the threshold's
-// key.  A histogram of all keys, scanned by a kernel of its own that moved the
+// of its n tiles (more than order_aim), or n / kListShare if that is more.  The
+// quantile of 64 listed keys, spread over the sub-lists: every workgroup draws the
+// same sample (one 8-byte load per lane) and ranks it without LDS.  The count
+// taken scatters by up to 6 % of n, which is a third of itself where an eighth of
+// the list is taken, and costs nothing.  At least one tile is taken: the one whose
+// entry has the threshold's key.  A histogram of all keys, scanned by a kernel of its own that moved the
 // chosen tiles to a work list and the others on, took 5 us of each 20 to 27 us
 // iteration: 2D lognormal 4096^2 14.5 -> 11.2 ms, 1500^2 4.8 -> 4.0, maze 256^3
 // 5.0 -> 4.5, adjoint of 50 receivers at 4096^2 10.7 -> 8.8.  Only an adjoint
 // that starts with tens of thousands of tiles queued was faster with it (dense
-// dL/dphi at 4096^2 16.8 ms, now 23.8: sending a tile on takes two atomics here,
+// dL/dphi at 4096^2 16.8 ms, now 23.5: sending a tile on takes two atomics here,
 // where nobody else added to the list there; without the share it took 28.8).
+// Against first-in first-out (every listed tile in every launch): 2D lognormal
+// 4096^2 10.9 ms against 15.5, 3D lognormal 320^3 7.1 against 9.5, 192^3 2.46
+// against 2.60; maze 256^3 4.03 against 3.96, layered 192^3 1.42 against 1.40; one
+// front at constant speed, 256^3, 2.17 against 1.88.
 constexpr int kListShare = 8;
 __device__ __forceinline__ uint32_t sampled_threshold(const Sched& a, const int* s_len, int n) {
     const int lane = threadIdx.x & 63;

@@ -57,7 +57,7 @@ struct TileIter : Sched {
     const T* F;
     T* phi;
     uint8_t* lab;
-    const T* cells;  // tile-major cell values (k_build_cells), read by detection and the remedy visits
+    const T* cells;  // tile-major cell values (k_tile_init), read by detection and the remedy visits
     int early;       // merged update step: revisits count as early remedy evaluations
 };
 
