@@ -34,13 +34,13 @@ constexpr Walk walk_of(uint32_t k, uint32_t outer, int steps) {
 
 // Planes per walk: the two values at its ends are read by the next walk too, so
 // long walks, but at least half a million lanes (four waves for each of the
-// 1024 SIMDs twice over), and no more than eight planes (16 M nodes: 257^3
-// float 100 us at 1, 89 at 2, 73 at 4 and 8, 78 at 16; 65280 x 257 double 125,
-// 100, 101, 105, 110).  With fewer than sixteen nodes a plane the lanes of a
-// wave read as many lines as they walk: two planes (16 M x 1 float 75 us at 1, 62
-// at 2, 136 at 8; 2 M x 8 double 109 at 1 and 2, 121 at 8).
+// 1024 SIMDs twice over).  Measured at 16 M nodes, 1 / 4 / 16 planes: 10485 x 40 x
+// 40 float 91, 66, 63 us, 65280 x 257 double 125, 101, 110; 200 x 333 x 250 float on
+// inputs not read before 83.3 us at 8, 81.6 at 16.  With fewer than sixteen nodes
+// a plane the lanes of a wave read as many lines as they walk: two planes (16 M x 1
+// float 75 us at 1, 62 at 2, 136 at 8; 2 M x 8 double 109 at 1 and 2, 121 at 8).
 constexpr int walk_steps(int64_t n, int64_t plane) {
-    const int64_t s = n >> 19, most = plane < 16 ? 2 : 8;
+    const int64_t s = n >> 19, most = plane < 16 ? 2 : 16;
     return s < 1 ? 1 : static_cast<int>(s < most ? s : most);
 }
 
