@@ -285,7 +285,7 @@ typedef struct {
  * candidate configurations on it (each solved once to warm up, then the
  * best of two timed solves; device time from HIP events on opt->stream):
  * first the tile shape and inner-iteration cap, then, for that shape, the
- * ordered remedy's per-launch minimum (half, the default and twice the
+ * ordered visits' per-launch target order_min (half, the default and twice the
  * default; not with EIK_FLAG_FIFO_REMEDY or EIK_FLAG_SKIP_REMEDY) and the
  * persistent workgroups per launch (1024, 1536, 2048).  Not in the paper: its
  * run times depend on the GPU's work-group size, and the tile shape and

@@ -1,5 +1,5 @@
 // eik_tune: per-problem choice of the tile variant's schedule -- tile shape
-// and inner-iteration cap, then the ordered remedy's per-launch minimum and
+// and inner-iteration cap, then the ordered visits' per-launch target and
 // the persistent workgroups per launch -- by timing candidates with HIP events
 // on the caller's stream.  Choices are cached per (ndim, dtype, log2 N,
 // per-axis spacing or not, remedy schedule flags) for the process.
@@ -35,7 +35,7 @@ std::map<TuneKey, Choice>& tune_cache() {
 }
 
 // Flags that change what a tile solve does (and so which shape is fastest);
-// with these the remedy is not ordered, so its per-launch minimum is not searched.
+// with these the visits are not ordered, or end before the remedy: no target is searched.
 constexpr uint32_t kScheduleFlags = EIK_FLAG_SKIP_REMEDY | EIK_FLAG_FIFO_REMEDY;
 // Flags a cached choice belongs to.
 constexpr uint32_t kCacheFlags = kScheduleFlags | EIK_FLAG_NO_EARLY_REMEDY;
@@ -182,8 +182,8 @@ EIK_API eik_status eik_tune(const void* F, int32_t ndim, const int64_t* dims, do
         const eik_status rc = trial(c);
         if (rc != EIK_OK) return rc;
     }
-    // launch parameters for the chosen shape: the ordered remedy's per-launch
-    // minimum (when the remedy runs ordered), then the workgroups per launch
+    // launch parameters for the chosen shape: the ordered visits' per-launch
+    // target (where visits run ordered), then the workgroups per launch
     const Choice shape = pick;
     if (!(base.flags & kScheduleFlags)) {
         const int om = order_min_of(ndim, 0);
